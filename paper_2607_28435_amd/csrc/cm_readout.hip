@@ -36,7 +36,8 @@ template <> struct rd<double2> {
 
 // Per-instance readout scalars.
 struct ReadConst {
-  double k0, eta, alpha, sfac;   // sfac = sqrt(M) / (s pi)
+  double k0, alpha, sfac;        // sfac = sqrt(M) / (s pi)
+  StrikeStep step;               // 2 pi / eta
   int64_t us;                    // k_u = k0 + lambda (u - us): the default grid is centred on ln S0
   int n;
   double2 ro;                    // exp(-i v0 k0)
@@ -50,7 +51,7 @@ __device__ __forceinline__ ReadConst read_const(const cm_problem &pr, int n) {
   // ln S0 + lambda (u - M/2) with an exact integer offset
   c.k0 = k0_is_default(pr) ? log(pr.S0) : pr.k0;
   c.us = k0_is_default(pr) ? ((int64_t)1 << (n - 1)) : 0;
-  c.eta = pr.eta;
+  c.step = strike_step(pr.eta);
   c.n = n;
   c.alpha = pr.alpha;
   c.sfac = ldexp((n & 1) ? M_SQRT2 : 1.0, n >> 1) / ((simpson ? 1.0 : 2.0) * M_PI);
@@ -70,7 +71,7 @@ __device__ __forceinline__ ReadConst read_const(const cm_problem &pr, int n) {
 }
 
 __device__ __forceinline__ double read_price(const ReadConst &c, int64_t u, double2 yu, int absval) {
-  const double k = strike_log(c.k0, c.eta, c.n, (double)(u - c.us));
+  const double k = strike_log(c.k0, c.step, c.n, (double)(u - c.us));
   if (absval) return exp(-c.alpha * k) * c.sfac * hypot(yu.x, yu.y);
   double2 ro = c.ro;
   if (c.alt && (u & 1)) ro = cmk(-ro.x, -ro.y);
@@ -91,6 +92,12 @@ template <> constexpr int rd_lds<double2>() { return 64 * 1024; }
 // then costs r_5 multiply-adds instead of a contraction through all n cores.
 constexpr int TB_LO = 5, TB_H = 12, TB_K = 2;
 constexpr int TB_MID = 1 << (TB_H - TB_LO);
+// A block of RD_WG RD_SPT strikes decides between tree and plain contraction as a whole (the
+// two add in different orders). Its strikes go to one workgroup when the blocks fill the chip,
+// else to several, of four rows of RD_WG strikes or of one: one instance's 4096 strikes on one
+// workgroup left 255 CUs idle (n = 30 in FP64, 4096 strikes spread over the window: 644 ->
+// 66 us), and 256 instances of 513 strikes took their three rows one after the other.
+constexpr int RD_FILL = 512;
 
 // Contracts one strike: v <- Y_l[:, bit_l, :] v from l = n-1 down to 0; returns y_u.
 // Core l starts at base + off(l) and holds [rk[l]][2][rk[l+1]] values.
@@ -189,12 +196,16 @@ template <typename T, int RM>
 __global__ __launch_bounds__(RD_WG) void k_readout(TTView y, const cm_problem *__restrict__ prob,
                                                    const int64_t *__restrict__ strike_idx, int nk,
                                                    double *__restrict__ prices, int32_t *__restrict__ status,
-                                                   int rm_lo, int absval) {
+                                                   int rm_lo, int absval, int rows, int parts) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ int32_t s_off[CM_MAX_N + 1], s_rk[CM_MAX_N + 1];
   __shared__ int64_t s_goff[CM_MAX_N];   // the cores' offsets in global memory
   __shared__ int s_ok;
   const int b = blockIdx.y;
+  const int blk = blockIdx.x / parts, part = blockIdx.x % parts;
+  const int s0 = blk * RD_WG * RD_SPT;
+  const int t0 = part * rows, t1 = t0 + rows;   // this workgroup's rows of the block
+  if (s0 + t0 * RD_WG >= nk) return;
   const int n = y.n[b];
   const int32_t *rk = y.rk(b);
   // this instantiation serves instances whose largest bond lies in (rm_lo, RM]
@@ -243,8 +254,7 @@ __global__ __launch_bounds__(RD_WG) void k_readout(TTView y, const cm_problem *_
   const cm_problem pr = prob[b];
   const ReadConst rc = read_const(pr, n);
   const int64_t M = (int64_t)1 << n;
-  const int s0 = blockIdx.x * RD_WG * RD_SPT;
-  // this workgroup's strikes; the range of their high parts decides the prefix tree. Each
+  // the block's strikes; the range of their high parts decides the prefix tree. Each
   // lane reduces its strikes, the wave reduces by shuffles, and one lane per wave updates
   // the workgroup's range: atomics from every lane to one LDS word serialise and cost more
   // than the rest of the read-out.
@@ -331,6 +341,7 @@ __global__ __launch_bounds__(RD_WG) void k_readout(TTView y, const cm_problem *_
     for (int t = 0; t < RD_SPT; ++t) {
       const int s = s0 + t * RD_WG + tid;
       const int64_t u = uu[t];
+      if (t < t0 || t >= t1) continue;
       if (s >= nk) break;
       const T *lo = Lo + (int)(u & 31) * r5;
       const T *mr = MR + (((int)((u >> TB_H) - hmin) * TB_MID) + (int)((u >> TB_LO) & (TB_MID - 1))) * r5;
@@ -340,11 +351,12 @@ __global__ __launch_bounds__(RD_WG) void k_readout(TTView y, const cm_problem *_
     }
     return;
   }
-#pragma unroll
-  for (int t = 0; t < RD_SPT; ++t) {
+  // the index is read again: these rows are not unrolled, and uu is indexed by constants only
+#pragma unroll 1
+  for (int t = t0; t < t1 && t < RD_SPT; ++t) {
     const int s = s0 + t * RD_WG + (int)threadIdx.x;
     if (s >= nk) break;
-    const int64_t u = uu[t];
+    const int64_t u = strike_idx[(int64_t)b * nk + s];
     double price;
     if (u < 0 || u >= M || pr.n != n) {
       price = NAN;
@@ -421,7 +433,12 @@ static cm_status readout(const cm_tt_batch *y, const cm_problem *prob, const int
   if (y->batch > 65535) return CM_E_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   TTView v = tt_view(y);
-  const dim3 grid((unsigned)((nk + RD_WG * RD_SPT - 1) / (RD_WG * RD_SPT)), (unsigned)y->batch);
+  const int blocks = (nk + RD_WG * RD_SPT - 1) / (RD_WG * RD_SPT);
+  const int64_t wgs = (int64_t)blocks * y->batch;
+  const int used = blocks > 1 ? RD_SPT : (nk + RD_WG - 1) / RD_WG;   // rows of a block that hold strikes
+  const int rows = wgs >= RD_FILL ? RD_SPT : wgs * ((used + 3) / 4) >= RD_FILL ? 4 : 1;
+  const int parts = (used + rows - 1) / rows;
+  const dim3 grid((unsigned)blocks * parts, (unsigned)y->batch);
   const int cap = y->cap_rank;
   // one-lane-per-strike kernels by bound on the largest bond; the lane-group kernel takes
   // the rest
@@ -432,23 +449,23 @@ static cm_status readout(const cm_tt_batch *y, const cm_problem *prob, const int
     CM_HIP_CHECK(cm_allow_lds(k_readout<float2, 16>, L));
     CM_HIP_CHECK(cm_allow_lds(k_readout<float2, 32>, L));
     hipLaunchKernelGGL((k_readout<float2, 8>), grid, dim3(RD_WG), L, s, v, prob, strike_idx, nk, prices, status, 0,
-                       absval);
+                       absval, rows, parts);
     if (cap > 8)
       hipLaunchKernelGGL((k_readout<float2, 16>), grid, dim3(RD_WG), L, s, v, prob, strike_idx, nk, prices, status, 8,
-                         absval);
+                         absval, rows, parts);
     if (cap > 16)
       hipLaunchKernelGGL((k_readout<float2, 32>), grid, dim3(RD_WG), L, s, v, prob, strike_idx, nk, prices, status, 16,
-                         absval);
+                         absval, rows, parts);
     fast_max = 32;
   } else {
     constexpr int L = rd_lds<double2>();
     CM_HIP_CHECK(cm_allow_lds(k_readout<double2, 8>, L));
     CM_HIP_CHECK(cm_allow_lds(k_readout<double2, 16>, L));
     hipLaunchKernelGGL((k_readout<double2, 8>), grid, dim3(RD_WG), L, s, v, prob, strike_idx, nk, prices, status, 0,
-                       absval);
+                       absval, rows, parts);
     if (cap > 8)
       hipLaunchKernelGGL((k_readout<double2, 16>), grid, dim3(RD_WG), L, s, v, prob, strike_idx, nk, prices, status, 8,
-                         absval);
+                         absval, rows, parts);
     fast_max = 16;
   }
   CM_LAUNCH_CHECK();
@@ -533,7 +550,7 @@ __global__ __launch_bounds__(256) void k_shot_price(const cm_problem *__restrict
     set_status(status, b, CM_E_INVALID);
   } else {
     const ReadConst rc = read_const(pr, n);
-    const double k = strike_log(rc.k0, rc.eta, rc.n, (double)(u - rc.us));
+    const double k = strike_log(rc.k0, rc.step, rc.n, (double)(u - rc.us));
     const double c = (double)counts[(int64_t)b * nk + s];
     price = exp(-rc.alpha * k) * rc.sfac * sqrt(nv * c / (double)R);
   }

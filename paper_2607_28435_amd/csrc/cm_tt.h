@@ -62,18 +62,30 @@ __host__ __device__ __forceinline__ void drift_angle(double eta, double lnS0, do
 // and cancel (on a grid centred far from the money both are ~2^(n/2); rounding lambda first
 // would cost |lambda u| ulp(1), 4e-11 at n = 40, and the damping factor alpha times that).
 #define CM_2PI_LO 2.4492935982947064e-16
-__host__ __device__ __forceinline__ double strike_log(double k0, double eta, int n, double u) {
+struct StrikeStep {
+  double c, cl;   // 2 pi / eta = c + cl
+};
+__host__ __device__ __forceinline__ StrikeStep strike_step(double eta) {
 #pragma clang fp contract(off)
-  const double c = CM_2PI / eta;
-  const double cl = (fma(-c, eta, CM_2PI) + CM_2PI_LO) / eta;   // 2 pi / eta = c + cl
+  StrikeStep s;
+  s.c = CM_2PI / eta;
+  s.cl = (fma(-s.c, eta, CM_2PI) + CM_2PI_LO) / eta;
+  return s;
+}
+// The step is a per-problem constant: forming it per strike cost two FP64 divisions each.
+__host__ __device__ __forceinline__ double strike_log(double k0, const StrikeStep &st, int n, double u) {
+#pragma clang fp contract(off)
   double p, e;
-  two_prod(c, u, p, e);
-  e = fma(cl, u, e);
+  two_prod(st.c, u, p, e);
+  e = fma(st.cl, u, e);
   p = ldexp(p, -n);
   e = ldexp(e, -n);
   double sm, t;
   two_sum(k0, p, sm, t);
   return sm + (t + e);
+}
+__host__ __device__ __forceinline__ double strike_log(double k0, double eta, int n, double u) {
+  return strike_log(k0, strike_step(eta), n, u);
 }
 
 // ------------------------------------------------------------------ rounding sweep
