@@ -313,16 +313,16 @@ cm_status cm_mlp_sync_bf16(const cm_mlp *net, void *stream);
 
 /* y[b] = network(x[b]) for b < B. x: device float [B][7] raw inputs; y: device float [B].
  * acts: device buffer of acts_bytes bytes. With acts_bytes >= cm_mlp_act_bytes(B) the
- * pre-activations Z1..Z4 are kept there for cm_mlp_backward (training: one launch per
- * layer). Otherwise (inference; acts may be NULL) one fused launch runs all five layers with
- * the activations kept on chip; its outputs equal the training path's to FP32 rounding (the
- * final 256-term sum is added in another order). */
+ * pre-activations Z1..Z4 are kept there for cm_mlp_backward (16-byte aligned). Otherwise
+ * (inference; acts may be NULL) nothing is kept. Either way one launch runs all five layers with
+ * the activations on chip; outputs of different batch sizes agree to FP32 rounding (the kernel
+ * for large batches adds in another order). */
 cm_status cm_mlp_forward(const cm_mlp *net, const float *x, int B, float *y, float *acts, size_t acts_bytes,
                          void *stream);
 
 /* grad = sum_b dy[b] * d y[b] / d params, overwriting grad (device float [CM_MLP_NPARAMS]).
  * acts: what cm_mlp_forward saved for the same x. ws: device workspace of
- * cm_mlp_act_bytes(B) / 2 bytes. Column sums over the batch use float atomics, so the
+ * cm_mlp_act_bytes(B) / 2 bytes (16-byte aligned). grad also serves as scratch during the call. Column sums over the batch use float atomics, so the
  * summation order (and the last bits) may vary between runs. */
 cm_status cm_mlp_backward(const cm_mlp *net, const float *x, const float *acts, const float *dy, int B, float *grad,
                           void *ws, size_t ws_bytes, void *stream);

@@ -3,14 +3,15 @@
 // in cm.h.
 //
 // The 256 x 256 layers are GEMMs on BF16 MFMA (v_mfma_f32_32x32x16_bf16) with FP32
-// accumulation. Forward and backward-data use k_gemm_ws (the weight matrix stays in LDS for
-// a persistent workgroup that streams 32-row tiles of activations); the weight gradients use
-// k_gemm (64 x 64 output tiles as four 32 x 32 wave tiles, 32-deep K slices of both operands
-// staged in LDS as BF16, split-K over the batch). An operand that comes from FP32
-// activations is split into hi + lo BF16 parts (two MFMAs per step), so its rounding error
-// is ~2^-16 instead of 2^-8. Operand lane layout (32x32x16): lane l holds
-// A[l % 32][8 (l / 32) + i] and B[8 (l / 32) + i][l % 32], i < 8; accumulator v of lane l is
-// C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
+// accumulation. An operand that comes from FP32 activations is split into hi + lo BF16 parts
+// (two MFMAs per step), so its rounding error is ~2^-16 instead of 2^-8. Operand lane layout
+// (32x32x16): lane l holds A[l % 32][8 (l / 32) + i] and B[8 (l / 32) + i][l % 32], i < 8;
+// accumulator v of lane l is C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
+//   k_mlp_fused  inference over many queries: five layers per tile of 64, two tiles in flight
+//   k_mlp_tile   five layers per tile of 32: small inference batches, and the training forward
+//                (which also stores the pre-activations)
+//   k_mlp_bwd    the backward-data chain per tile of 32, with the first layer's gradients
+//   k_wgrad      the other layers' gradients: sums over the batch of delta^T silu(Z)
 #include "cm_internal.h"
 
 namespace {
@@ -36,18 +37,12 @@ __host__ __device__ constexpr int wfrag(int n, int k) {
   return ((((n >> 5) * 16 + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (n & 31)) << 3) + (k & 7);
 }
 
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
 // SiLU from the hardware exp2 and reciprocal (a few ulps): for the activation operand of the
 // layer GEMMs, whose hi + lo BF16 split keeps about 2^-16 of it anyway. Large |z| behave:
 // exp2 overflows to inf and the reciprocal to 0 (z -> -inf), or exp2 goes to 0 (z -> +inf).
 __device__ __forceinline__ float silu_fast(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
-__device__ __forceinline__ float silu_grad_f(float z) {
-  const float s = 1.0f / (1.0f + expf(-z));
-  return s * (1.0f + z * (1.0f - s));
-}
-
 // float -> bf16 bits, round to nearest even (NaN stays NaN)
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -56,225 +51,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// ------------------------------------------------------------------ GEMM
-constexpr int GT = 64;        // tile edge
-constexpr int KC = 32;        // K slice staged per step
-constexpr int KP = KC + 8;    // LDS row pitch (bf16 elements): 80 bytes, 16-byte aligned rows
-
-enum { A_ROWMAJOR = 0, A_COLMAJOR = 1 };        // A[m lda + k] or A[k lda + m]  (FP32)
-enum { B_F32_KN = 0, B_BF16_NK = 1, B_BF16_KN = 2 };  // B[k ldb + n] fp32, B[n ldb + k] bf16, B[k ldb + n] bf16
-enum { F_NONE = 0, F_SILU = 1 };
-enum { E_BIAS_STORE = 0, E_DSILU_STORE = 1, E_ATOMIC_ADD = 2 };
-
-struct GemmArgs {
-  const float *A;
-  int lda;
-  const void *B;
-  int ldb;
-  int M, N, K, kspan;   // kspan: K range per blockIdx.z
-  float *C;
-  int ldc;
-  const float *bias;    // E_BIAS_STORE
-  const float *Z;       // E_DSILU_STORE: multiply by silu'(Z[m ldc + n])
-};
-
-template <int AL, int AF, bool ASPLIT, int BK, int BF, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __align__(16) uint16_t As[2][GT][KP];
-  __shared__ __align__(16) uint16_t Bs[GT][KP];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int n0 = blockIdx.x * GT, m0 = blockIdx.y * GT;
-  const int kbeg = blockIdx.z * g.kspan;
-  const int kend = min(g.K, kbeg + g.kspan);
-  f32x16 acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  for (int k0 = kbeg; k0 < kend; k0 += KC) {
-    // ---- stage A (64 x 32)
-    if (AL == A_ROWMAJOR) {
-      const int m = tid >> 2, k8 = (tid & 3) * 8;
-      const int gm = m0 + m;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gk = k0 + k8 + i;
-        float v = (gm < g.M && gk < kend) ? g.A[(int64_t)gm * g.lda + gk] : 0.0f;
-        if (AF == F_SILU) v = silu_f(v);
-        const uint16_t hi = f2bf(v);
-        As[0][m][k8 + i] = hi;
-        if (ASPLIT) As[1][m][k8 + i] = f2bf(v - bf2f(hi));
-      }
-    } else {
-      const int k = tid >> 3, m8 = (tid & 7) * 8;
-      const int gk = k0 + k;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gm = m0 + m8 + i;
-        float v = (gm < g.M && gk < kend) ? g.A[(int64_t)gk * g.lda + gm] : 0.0f;
-        if (AF == F_SILU) v = silu_f(v);
-        const uint16_t hi = f2bf(v);
-        As[0][m8 + i][k] = hi;
-        if (ASPLIT) As[1][m8 + i][k] = f2bf(v - bf2f(hi));
-      }
-    }
-    // ---- stage B (32 x 64) as Bs[n][k]
-    if (BK == B_BF16_NK) {
-      const int n = tid >> 2, k8 = (tid & 3) * 8;
-      const int gn = n0 + n;
-      const uint16_t *Bb = (const uint16_t *)g.B;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gk = k0 + k8 + i;
-        Bs[n][k8 + i] = (gn < g.N && gk < kend) ? Bb[(int64_t)gn * g.ldb + gk] : (uint16_t)0;
-      }
-    } else {
-      const int k = tid >> 3, n8 = (tid & 7) * 8;
-      const int gk = k0 + k;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gn = n0 + n8 + i;
-        uint16_t h = 0;
-        if (gn < g.N && gk < kend) {
-          if (BK == B_BF16_KN) {
-            h = ((const uint16_t *)g.B)[(int64_t)gk * g.ldb + gn];
-          } else {
-            float v = ((const float *)g.B)[(int64_t)gk * g.ldb + gn];
-            if (BF == F_SILU) v = silu_f(v);
-            h = f2bf(v);
-          }
-        }
-        Bs[n8 + i][k] = h;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KC; kk += 16) {
-      const int kq = kk + 8 * (lane >> 5);
-      const s16x8 bv = *(const s16x8 *)&Bs[wn * 32 + (lane & 31)][kq];
-      const s16x8 av = *(const s16x8 *)&As[0][wm * 32 + (lane & 31)][kq];
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
-                                                    acc, 0, 0, 0);
-      if (ASPLIT) {
-        const s16x8 al = *(const s16x8 *)&As[1][wm * 32 + (lane & 31)][kq];
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, al),
-                                                      __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  // ---- epilogue
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int m = m0 + wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    const int n = n0 + wn * 32 + (lane & 31);
-    if (m < g.M && n < g.N) {
-      float* c = g.C + (int64_t)m * g.ldc + n;
-      if (EPI == E_BIAS_STORE) *c = acc[v] + g.bias[n];
-      else if (EPI == E_DSILU_STORE) *c = acc[v] * silu_grad_f(g.Z[(int64_t)m * g.ldc + n]);
-      else atomicAdd(c, acc[v]);
-    }
-  }
-}
-
-// Weight-stationary layer for the batch dimension: C[M x 256] = epi(op(A) W'), with the
-// whole 256 x 256 BF16 weight matrix held in LDS (Ws[n][k], 132 KB) for the workgroup's
-// lifetime and the workgroup looping over 32-row tiles of A. Each wave computes 32 rows x 64
-// columns (two 32 x 32 accumulators); it reads its A operand straight from global memory
-// (FP32, split into hi + lo BF16 in registers; the four waves read the same rows, which
-// the L1 serves).
-//   W_NK: W' = W^T, Ws[n][k] = W[n][k]   (forward: z = a W^T + b)
-//   W_KN: W' = W,   Ws[n][k] = W[k][n]   (backward data: delta W)
-enum { W_NK = 0, W_KN = 1 };
-constexpr int WSP = NW + 8;   // LDS row pitch of Ws (bf16): 528 bytes, 16-byte aligned
-
-// Up to WS_TILES row tiles are in flight per workgroup: wave w computes columns
-// 128 (w % 2) .. +127 of tiles blockIdx.x + (w / 2 + WS_TILES i) gridDim.x, so the LDS copy of
-// the weights serves 16 waves (four per SIMD) on large batches while small batches still
-// spread one tile per workgroup over the CUs; each activation element is transformed
-// (SiLU, hi/lo split) by the two waves of its tile.
-constexpr int WS_TILES = 8;
-constexpr int WS_THREADS = 1024;
-
-template <int WL, int AF, int EPI>
-__global__ __launch_bounds__(WS_THREADS) void k_gemm_ws(const float *__restrict__ A, const uint16_t *__restrict__ W,
-                                                        int M, float *__restrict__ C, const float *__restrict__ bias,
-                                                        const float *__restrict__ Z) {
-  extern __shared__ __align__(16) uint16_t Ws[];   // [NW][WSP]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // W is in fragment order: 16-byte piece c holds row 32 (c / 1024) + c mod 32, columns
-  // 16 ((c / 64) mod 16) + 8 ((c / 32) mod 2) .. +7
-  if (WL == W_NK) {
-    for (int c = tid; c < NW * NW / 8; c += WS_THREADS) {
-      const int blk = c >> 6, ln = c & 63;
-      const int n = 32 * (blk >> 4) + (ln & 31), k8 = 16 * (blk & 15) + 8 * (ln >> 5);
-      *(uint4 *)&Ws[n * WSP + k8] = *(const uint4 *)&W[8 * c];
-    }
-  } else {
-    for (int e = tid; e < NW * NW; e += WS_THREADS) {
-      const int blk = e >> 9, ln = (e >> 3) & 63;
-      const int row = 32 * (blk >> 4) + (ln & 31), col = 16 * (blk & 15) + 8 * (ln >> 5) + (e & 7);
-      Ws[col * WSP + row] = W[e];
-    }
-  }
-  __syncthreads();
-  const int ntiles = (M + 31) / 32;
-  const int col0 = (wave & 1) * 128;
-  for (int t = blockIdx.x + (wave >> 1) * gridDim.x; t < ntiles; t += gridDim.x * WS_TILES) {
-    const int row = t * 32 + (lane & 31);
-    const bool rok = row < M;
-    f32x16 acc[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[h][v] = 0.0f;
-    const float *arow = A + (int64_t)(rok ? row : 0) * NW;
-#pragma unroll 2
-    for (int kk = 0; kk < NW; kk += 16) {
-      const int kq = kk + 8 * (lane >> 5);
-      float a[8];
-      if (rok) {
-        const float4 x0 = *(const float4 *)&arow[kq], x1 = *(const float4 *)&arow[kq + 4];
-        a[0] = x0.x; a[1] = x0.y; a[2] = x0.z; a[3] = x0.w; a[4] = x1.x; a[5] = x1.y; a[6] = x1.z; a[7] = x1.w;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = 0.0f;
-      }
-      s16x8 ah, al;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        // hi + lo BF16 parts by the hardware conversion (v_cvt_pk_bf16_f32); the split only
-        // has to represent v, so its rounding mode does not matter
-        const float v = (AF == F_SILU) ? silu_fast(a[i]) : a[i];
-        const uint16_t h = __builtin_bit_cast(uint16_t, (__bf16)v);
-        ah[i] = (short)h;
-        al[i] = (short)__builtin_bit_cast(uint16_t, (__bf16)(v - bf2f(h)));
-      }
-      const bf16x8 AH = __builtin_bit_cast(bf16x8, ah), AL = __builtin_bit_cast(bf16x8, al);
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const s16x8 b = *(const s16x8 *)&Ws[(col0 + 32 * h + (lane & 31)) * WSP + kq];
-        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AH, __builtin_bit_cast(bf16x8, b), acc[h], 0, 0, 0);
-        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AL, __builtin_bit_cast(bf16x8, b), acc[h], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int m = t * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      if (m < M) {
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          const int n = col0 + 32 * h + (lane & 31);
-          const float val = acc[h][v];
-          float *c = C + (int64_t)m * NW + n;
-          if (EPI == E_BIAS_STORE) *c = val + bias[n];
-          else *c = val * silu_grad_f(Z[(int64_t)m * NW + n]);
-        }
-      }
-    }
-  }
-}
-constexpr size_t WS_LDS = sizeof(uint16_t) * NW * WSP;
 
 // ------------------------------------------------------------------ fused inference
 // The whole network for tiles of FM = 64 queries, with no activation leaving the CU. Each
@@ -531,85 +307,450 @@ __global__ __launch_bounds__(512, 1) void k_mlp_fused(const float *__restrict__ 
   }
 }
 
-// ------------------------------------------------------------------ small layers
-// Z1[b][n] = b1[n] + sum_i W1[n][i] xn[b][i]
-__global__ void k_mlp_in(const float *__restrict__ x, int B, const float *__restrict__ p, cm_mlp net,
-                         float *__restrict__ Z1) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= (int64_t)B * NW) return;
-  const int b = (int)(e / NW), n = (int)(e % NW);
-  float acc = p[OFF_B1 + n];
+// ------------------------------------------------------------------ tiles of 32 rows
+// One workgroup of eight waves takes 32 rows through a chain of 256 x 256 products; wave w
+// owns neurons 32 w .. 32 w + 31 of every layer (one 32 x 32 accumulator per operand part).
+// As in k_mlp_fused the products are transposed (weights are the A operand, in fragment order;
+// the rows' values the B operand, hi and lo parts in LDS). All 16 weight fragments of the next
+// layer are loaded while the present one finishes, and the values alternate between two LDS
+// buffers, so a layer costs one barrier. 8192 rows are 256 tiles, one per CU; a launch per layer
+// with the weights staged in LDS put one 32-row tile on two of sixteen waves behind 128 KB of
+// staging. 8192 rows: forward with the pre-activations stored 18.5 us (58 before), backward
+// chain 31 us (107 before, its first-layer gradients included); 777 rows of inference 9.6 us
+// (27 with tiles of 64). Bound by the latency of a layer (fragments, products, epilogue).
+constexpr int TM = 32;
+constexpr int TWG = 512;
+constexpr int TKS = NW / 16;                                        // K steps per layer
+constexpr size_t TILE_BUF = (size_t)2 * TM * FP;                    // hi and lo parts (uint16)
+constexpr size_t TILE_LDS = sizeof(uint16_t) * 2 * TILE_BUF;
+
+// hi + lo parts of four consecutive neurons' values of row r into a tile buffer
+__device__ __forceinline__ void put4(uint16_t *buf, int r, int n, const float *v) {
+  uint16_t h[4], lo[4];
 #pragma unroll
-  for (int i = 0; i < NIN; ++i) acc += p[OFF_W1 + n * NIN + i] * ((x[(int64_t)b * NIN + i] - net.shift[i]) * net.scale[i]);
-  Z1[e] = acc;
-}
-
-// y[b] = b5 + sum_n W5[n] silu(Z4[b][n]); one wavefront per row
-__global__ void k_mlp_out(const float *__restrict__ Z4, int B, const float *__restrict__ p, float *__restrict__ y) {
-  const int b = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (b >= B) return;
-  float acc = 0.0f;
-  for (int n = lane; n < NW; n += 64) acc += p[OFF_W5 + n] * silu_f(Z4[(int64_t)b * NW + n]);
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) y[b] = acc + p[OFF_B5];
-}
-
-// delta4[b][n] = dy[b] W5[n] silu'(Z4[b][n])
-__global__ void k_out_back(const float *__restrict__ Z4, const float *__restrict__ dy, int B,
-                           const float *__restrict__ p, float *__restrict__ d4) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= (int64_t)B * NW) return;
-  const int b = (int)(e / NW), n = (int)(e % NW);
-  d4[e] = dy[b] * p[OFF_W5 + n] * silu_grad_f(Z4[e]);
-}
-
-// out[n] += sum_{b in chunk} w[b] f(X[b][n])  (w = NULL: weight 1); blockDim = 256 (one
-// thread per column), blockIdx.x = row chunk
-template <int F>
-__global__ void k_colsum(const float *__restrict__ X, const float *__restrict__ w, int B, int rows_per,
-                         float *__restrict__ out) {
-  const int n = threadIdx.x;
-  const int b0 = blockIdx.x * rows_per, b1 = min(B, b0 + rows_per);
-  float acc = 0.0f;
-  for (int b = b0; b < b1; ++b) {
-    float v = X[(int64_t)b * NW + n];
-    if (F == F_SILU) v = silu_f(v);
-    acc += (w ? w[b] : 1.0f) * v;
+  for (int j = 0; j < 4; ++j) {
+    h[j] = __builtin_bit_cast(uint16_t, (__bf16)v[j]);
+    lo[j] = __builtin_bit_cast(uint16_t, (__bf16)(v[j] - bf2f(h[j])));
   }
-  atomicAdd(out + n, acc);
+  const int off = r * FP + n;
+  *(uint2 *)&buf[off] = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+  *(uint2 *)&buf[TM * FP + off] = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
 }
 
-// gb5 += sum_b dy[b]
-__global__ void k_sum(const float *__restrict__ v, int B, float *__restrict__ out) {
-  float acc = 0.0f;
-  for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < B; b += gridDim.x * blockDim.x) acc += v[b];
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) atomicAdd(out, acc);
+// the 16 weight fragments of neuron block w (fragment-ordered matrix W)
+__device__ __forceinline__ void load_frags(const uint16_t *__restrict__ W, int w, int lane, s16x8 *f) {
+  const uint16_t *src = W + (int64_t)w * TKS * WFB + 8 * lane;
+#pragma unroll
+  for (int ks = 0; ks < TKS; ++ks) f[ks] = *(const s16x8 *)(src + ks * WFB);
 }
 
-// gW1[n][i] += sum_b d1[b][n] xn[b][i], gb1[n] += sum_b d1[b][n]
-__global__ void k_in_back(const float *__restrict__ d1, const float *__restrict__ x, int B, int rows_per, cm_mlp net,
-                          float *__restrict__ grad) {
-  const int n = threadIdx.x;
-  const int b0 = blockIdx.x * rows_per, b1 = min(B, b0 + rows_per);
-  float gw[NIN], gb = 0.0f;
+// acc[0] += W_block hi(values), acc[1] += W_block lo(values) over all K: two independent chains
+__device__ __forceinline__ void tile_product(const uint16_t *buf, int lane, const s16x8 *f, f32x16 *acc) {
+  const uint16_t *src = buf + (lane & 31) * FP + 8 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < NIN; ++i) gw[i] = 0.0f;
-  for (int b = b0; b < b1; ++b) {
-    const float d = d1[(int64_t)b * NW + n];
-    gb += d;
+  for (int ks = 0; ks < TKS; ++ks) {
+    const bf16x8 A = __builtin_bit_cast(bf16x8, f[ks]);
+    const s16x8 bh = *(const s16x8 *)(src + 16 * ks), bl = *(const s16x8 *)(src + TM * FP + 16 * ks);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, bh), acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, bl), acc[1], 0, 0, 0);
+  }
+}
+
+// y[b] = network(x[b]); with KEEP the pre-activations Z1..Z4 go to Z ([4][B][256]).
+template <bool KEEP>
+__global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, int B, const float *__restrict__ p,
+                                                  const uint16_t *__restrict__ wbf, cm_mlp net,
+                                                  float *__restrict__ y, float *__restrict__ Z) {
+  extern __shared__ __align__(16) uint16_t tl[];
+  __shared__ __align__(16) float w1s[NW * NIN], bsh[4][NW], w5s[NW];
+  __shared__ float xs[TM][NIN + 1], ys[8][TM];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l32 = lane & 31, hi32 = lane >> 5;
+  const int q0 = blockIdx.x * TM, q = q0 + l32;
+  s16x8 f[TKS];
+  load_frags(wbf, w, lane, f);
+  for (int e = tid; e < NW * NIN; e += TWG) w1s[e] = p[OFF_W1 + e];
+  for (int e = tid; e < NW; e += TWG) {
+    bsh[0][e] = p[OFF_B1 + e];
+    bsh[1][e] = p[off_b(2) + e];
+    bsh[2][e] = p[off_b(3) + e];
+    bsh[3][e] = p[off_b(4) + e];
+    w5s[e] = p[OFF_W5 + e];
+  }
+  if (tid < TM * NIN) {
+    const int r = tid / NIN, i = tid % NIN;
+    xs[r][i] = q0 + r < B ? (x[(int64_t)(q0 + r) * NIN + i] - net.shift[i]) * net.scale[i] : 0.0f;
+  }
+  __syncthreads();
+  f32x16 acc[2];
+  // accumulator v of this lane: neuron 32 w + 8 (v / 4) + 4 hi32 + v mod 4 of row l32
+  {
+    float xr[NIN];
 #pragma unroll
-    for (int i = 0; i < NIN; ++i) gw[i] += d * ((x[(int64_t)b * NIN + i] - net.shift[i]) * net.scale[i]);
+    for (int i = 0; i < NIN; ++i) xr[i] = xs[l32][i];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = 32 * w + 8 * g + 4 * hi32;
+      float wv[4 * NIN];   // rows n .. n + 3 of W1, contiguous
+#pragma unroll
+      for (int c = 0; c < NIN; ++c) {
+        const float4 t = *(const float4 *)&w1s[n * NIN + 4 * c];
+        wv[4 * c] = t.x; wv[4 * c + 1] = t.y; wv[4 * c + 2] = t.z; wv[4 * c + 3] = t.w;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float s = bsh[0][n + j];
+#pragma unroll
+        for (int i = 0; i < NIN; ++i) s += wv[j * NIN + i] * xr[i];
+        acc[0][4 * g + j] = s;
+      }
+    }
   }
 #pragma unroll
-  for (int i = 0; i < NIN; ++i) atomicAdd(grad + OFF_W1 + n * NIN + i, gw[i]);
-  atomicAdd(grad + OFF_B1 + n, gb);
+  for (int l = 2; l <= 5; ++l) {
+    // acc[0] holds z_{l-1}: store it, then either the output fold or the next product
+    float v[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = 32 * w + 8 * g + 4 * hi32;
+      if (KEEP && q < B)
+        *(float4 *)&Z[((int64_t)(l - 2) * B + q) * NW + n] =
+            make_float4(acc[0][4 * g], acc[0][4 * g + 1], acc[0][4 * g + 2], acc[0][4 * g + 3]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * g + j] = silu_fast(acc[0][4 * g + j]);
+    }
+    if (l == 5) {
+      float s = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += w5s[32 * w + 8 * (k >> 2) + 4 * hi32 + (k & 3)] * v[k];
+      s += __shfl_xor(s, 32, 64);
+      if (hi32 == 0) ys[w][l32] = s;
+    } else {
+      uint16_t *buf = tl + (l & 1) * TILE_BUF;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) put4(buf, l32, 32 * w + 8 * g + 4 * hi32, v + 4 * g);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 b4 = *(const float4 *)&bsh[l - 1][32 * w + 8 * g + 4 * hi32];
+        acc[0][4 * g] = b4.x; acc[0][4 * g + 1] = b4.y; acc[0][4 * g + 2] = b4.z; acc[0][4 * g + 3] = b4.w;
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[1][k] = 0.0f;
+      __syncthreads();
+      tile_product(buf, lane, f, acc);
+      if (l < 4) load_frags(wbf + (int64_t)(l - 1) * NW * NW, w, lane, f);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[0][k] += acc[1][k];
+    }
+  }
+  __syncthreads();
+  if (tid < TM && q0 + tid < B) {
+    float s = p[OFF_B5];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += ys[k][tid];
+    y[q0 + tid] = s;
+  }
 }
 
-__global__ void k_fill(float *__restrict__ a, int64_t n, float v) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    a[i] = v;
+// ------------------------------------------------------------------ backward
+// Where the transposed weight copies W4^T, W3^T, W2^T (fragment order) live during the backward
+// chain: in the gradient buffer, inside W3's and W4's gradients, which are only accumulated
+// after it. 16-byte aligned whatever the buffer's own alignment.
+__host__ __device__ inline uint16_t *grad_scratch(float *grad) {
+  return (uint16_t *)(((uintptr_t)(grad + off_w(3)) + 15) & ~(uintptr_t)15);
+}
+// Behind them, copies of the first layer's gradients (W1, b1), which the tiles of k_mlp_bwd add
+// to by turns: 256 tiles adding to each address serialised (59 us against 31 us at 8192 rows).
+// k_bwd_mid sums them and clears the space.
+constexpr int FIRST_COPIES = 16, FIRST_OFF = off_w(3) + 4 + 3 * NW * NW / 2, FIRST_N = off_w(2);
+static_assert(FIRST_OFF + FIRST_COPIES * FIRST_N <= OFF_W5, "the scratch fits before W5's gradient");
+
+// Transposes the BF16 copies (one 8 x 8 piece per thread) and clears the copies of the first
+// layer's gradients.
+__global__ __launch_bounds__(256) void k_bwd_prep(const uint16_t *__restrict__ wbf, uint16_t *__restrict__ wt,
+                                                  float *__restrict__ grad) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= 3 * NW * NW / 64) {   // 3 * 1024 pieces, then the copies
+    const int c = e - 3 * NW * NW / 64;
+    if (c < FIRST_COPIES * FIRST_N) grad[FIRST_OFF + c] = 0.0f;
+    return;
+  }
+  const int l = e >> 10, n0 = 8 * ((e >> 5) & 31), k0 = 8 * (e & 31);
+  s16x8 r[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = *(const s16x8 *)&wbf[l * NW * NW + wfrag(n0 + i, k0)];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    s16x8 c;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = r[i][j];
+    *(s16x8 *)&wt[l * NW * NW + wfrag(k0 + j, n0)] = c;
+  }
+}
+
+// Between the backward chain and k_wgrad: the first layer's gradients from their copies, and
+// zeros in every other gradient (each copy's element is cleared by the thread that read it).
+__global__ __launch_bounds__(256) void k_bwd_mid(float *__restrict__ grad) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < FIRST_N) {
+    float s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < FIRST_COPIES; ++c) s += grad[FIRST_OFF + c * FIRST_N + e];
+#pragma unroll
+    for (int c = 0; c < FIRST_COPIES; ++c) grad[FIRST_OFF + c * FIRST_N + e] = 0.0f;
+    grad[e] = s;
+  } else if (e < CM_MLP_NPARAMS && (e < FIRST_OFF || e >= FIRST_OFF + FIRST_COPIES * FIRST_N)) {
+    grad[e] = 0.0f;
+  }
+}
+
+// sigmoid from the hardware exp2 and reciprocal (see silu_fast)
+__device__ __forceinline__ float sig_fast(float z) {
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
+}
+__device__ __forceinline__ float silu_grad_fast(float z) {
+  const float s = sig_fast(z);
+  return s * (1.0f + z * (1.0f - s));
+}
+
+// delta_4 = dy W5 silu'(Z4), delta_{l-1} = (delta_l W_l) silu'(Z_{l-1}) for a tile of 32 rows;
+// delta_3 and delta_2 go to D ([2][B][256]), delta_1 stays on chip and is summed into W1's and
+// b1's gradients (FP32, one atomic per gradient and tile, to one of their copies).
+__global__ __launch_bounds__(TWG) void k_mlp_bwd(const float *__restrict__ x, const float *__restrict__ Z,
+                                                 const float *__restrict__ dy, int B, const float *__restrict__ p,
+                                                 const uint16_t *__restrict__ wt, cm_mlp net, float *__restrict__ D,
+                                                 float *__restrict__ grad) {
+  extern __shared__ __align__(16) uint16_t tl[];
+  __shared__ float xs[TM][8];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l32 = lane & 31, hi32 = lane >> 5;
+  const int q0 = blockIdx.x * TM, q = q0 + l32;
+  const bool ok = q < B;
+  const int64_t zrow = (int64_t)(ok ? q : 0) * NW, BN = (int64_t)B * NW;
+  s16x8 f[TKS];
+  load_frags(wt + 2 * NW * NW, w, lane, f);
+  if (tid < TM * 8) {
+    const int r = tid >> 3, i = tid & 7;
+    xs[r][i] = q0 + r >= B ? 0.0f : i == NIN ? 1.0f : (x[(int64_t)(q0 + r) * NIN + i] - net.shift[i]) * net.scale[i];
+  }
+  float v[16];
+  {
+    const float d = ok ? dy[q] : 0.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = 32 * w + 8 * g + 4 * hi32;
+      const float4 z = *(const float4 *)&Z[3 * BN + zrow + n];
+      v[4 * g] = d * p[OFF_W5 + n] * silu_grad_fast(z.x);
+      v[4 * g + 1] = d * p[OFF_W5 + n + 1] * silu_grad_fast(z.y);
+      v[4 * g + 2] = d * p[OFF_W5 + n + 2] * silu_grad_fast(z.z);
+      v[4 * g + 3] = d * p[OFF_W5 + n + 3] * silu_grad_fast(z.w);
+      put4(tl, l32, n, v + 4 * g);
+    }
+  }
+#pragma unroll
+  for (int l = 4; l >= 2; --l) {
+    const uint16_t *buf = tl + (l & 1) * TILE_BUF;
+    float4 z[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) z[g] = *(const float4 *)&Z[(l - 2) * BN + zrow + 32 * w + 8 * g + 4 * hi32];
+    f32x16 acc[2];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc[0][k] = acc[1][k] = 0.0f;
+    __syncthreads();
+    tile_product(buf, lane, f, acc);
+    if (l > 2) load_frags(wt + (int64_t)(l - 3) * NW * NW, w, lane, f);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      v[4 * g] = (acc[0][4 * g] + acc[1][4 * g]) * silu_grad_fast(z[g].x);
+      v[4 * g + 1] = (acc[0][4 * g + 1] + acc[1][4 * g + 1]) * silu_grad_fast(z[g].y);
+      v[4 * g + 2] = (acc[0][4 * g + 2] + acc[1][4 * g + 2]) * silu_grad_fast(z[g].z);
+      v[4 * g + 3] = (acc[0][4 * g + 3] + acc[1][4 * g + 3]) * silu_grad_fast(z[g].w);
+      const int n = 32 * w + 8 * g + 4 * hi32;
+      if (l > 2) {
+        put4(tl + ((l - 1) & 1) * TILE_BUF, l32, n, v + 4 * g);
+        if (ok) *(float4 *)&D[(4 - l) * BN + zrow + n] = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+      }
+    }
+  }
+  // delta_1 as FP32 rows of 260 in LDS (over both buffers, once every wave has read the last)
+  constexpr int DP = NW + 4;
+  static_assert(sizeof(float) * (TM * DP + 8 * NW) <= TILE_LDS, "delta_1 and the half sums fit the tile buffers");
+  float *d1 = (float *)tl, *half = d1 + TM * DP;
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < 4; ++g) *(float4 *)&d1[l32 * DP + 32 * w + 8 * g + 4 * hi32] =
+      make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+  __syncthreads();
+  const int n = tid & (NW - 1), r0 = (tid >> 8) * (TM / 2);
+  float gs[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) gs[i] = 0.0f;
+#pragma unroll
+  for (int r = 0; r < TM / 2; ++r) {
+    const float d = d1[(r0 + r) * DP + n];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) gs[i] += d * xs[r0 + r][i];
+  }
+  if (tid >= NW) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) half[i * NW + n] = gs[i];
+  }
+  __syncthreads();
+  if (tid < NW) {
+    float *first = grad + FIRST_OFF + (blockIdx.x % FIRST_COPIES) * FIRST_N;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      atomicAdd(first + (i < NIN ? OFF_W1 + n * NIN + i : OFF_B1 + n), gs[i] + half[i * NW + n]);
+  }
+}
+
+// Gradients of layers 2..5 from the batch: gW_l[m][n] += sum_b delta_l[b][m] silu(Z_{l-1}[b][n])
+// (delta split into hi + lo parts, the activation rounded to BF16), gb_l += sum_b delta_l[b],
+// gW5 += sum_b dy[b] silu(Z4[b]), gb5 += sum_b dy[b]. A workgroup takes one span of rows for one
+// layer and 128 x 128 tile. Workgroups go to the eight XCDs in turn, so the twelve tiles of a span
+// are numbered eight apart: they read the same rows and share one L2. The batch is the K dimension, so a lane's fragment is eight rows
+// of one column: eight dword loads whose lanes run along the row (128-byte segments), converted
+// in registers. Each wave converts one of the four 32-column blocks of either operand and
+// shares the fragments through LDS, so nothing is loaded or converted twice in a workgroup; the
+// next rows' loads are in flight during the products. delta_4 is formed here from dy and Z4.
+// 8192 rows take 35 us for all layers, about 10 of them the 6.3 M atomics of 32 spans (16 spans
+// 53 us: too few workgroups; 64 about 10 us more atomics); it is bound by the latency of a step's
+// loads. It replaces, per layer, a 64 x 64-tile kernel that converted each element in four
+// workgroups (44 us) and a column sum (19 us).
+constexpr int GWT = 128;                  // tile edge
+constexpr int GKR = 32;                   // rows per step
+constexpr int WG_SPANS = 32;              // spans of rows (see cm_mlp_backward)
+constexpr int XCDS = 8;
+__global__ __launch_bounds__(256) void k_wgrad(const float *__restrict__ Z, const float *__restrict__ dy,
+                                               const float *__restrict__ D, int B, int span,
+                                               const float *__restrict__ p, float *__restrict__ grad) {
+  __shared__ __align__(16) uint16_t fr[2][3][2][4][64 * 8];   // [buffer][A hi, A lo, B][K half][block][lane]
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hi32 = lane >> 5;
+  const int slot = blockIdx.x / XCDS, tile = slot % 12;
+  const int rbeg = (blockIdx.x % XCDS + XCDS * (slot / 12)) * span;
+  if (rbeg >= B) return;
+  const int layer = 4 - (tile >> 2);                          // 4, 3, 2
+  const int m0 = ((tile >> 1) & 1) * GWT, n0 = (tile & 1) * GWT;
+  const int64_t BN = (int64_t)B * NW;
+  const int rend = min(B, rbeg + span);
+  const int ca = m0 + 32 * wv + l32, cb = n0 + 32 * wv + l32;   // this lane's columns
+  const float *Asrc = layer == 4 ? Z + 3 * BN : D + (3 - layer) * BN;
+  const float *Bsrc = Z + (layer - 2) * BN;
+  const float w5 = layer == 4 ? p[OFF_W5 + ca] : 0.0f;
+  const bool sums = n0 == 0;              // these workgroups also add the bias gradients
+  float gb = 0.0f, g5 = 0.0f, gd = 0.0f;
+  struct Rows {
+    float a[2][8], b[2][8], d[2][8];
+  };
+  auto load = [&](int r0, Rows &t) {
+    if (r0 + GKR <= rend) {   // uniform: whole steps address their rows by constant offsets
+      const int64_t o = (int64_t)(r0 + 8 * hi32) * NW;
+      const float *pa = Asrc + o + ca, *pb = Bsrc + o + cb, *pd = dy + r0 + 8 * hi32;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          t.a[h][i] = pa[(16 * h + i) * NW];
+          t.b[h][i] = pb[(16 * h + i) * NW];
+          t.d[h][i] = layer == 4 ? pd[16 * h + i] : 1.0f;
+        }
+      return;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = r0 + 16 * h + 8 * hi32 + i;
+        const bool in = r < rend;
+        const int64_t o = (int64_t)(in ? r : rbeg) * NW;
+        t.a[h][i] = in ? Asrc[o + ca] : 0.0f;
+        t.b[h][i] = Bsrc[o + cb];
+        t.d[h][i] = !in ? 0.0f : layer == 4 ? dy[r] : 1.0f;
+      }
+  };
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.0f;
+  Rows cur, nxt;
+  load(rbeg, cur);
+  int b = 0;
+  for (int r0 = rbeg; r0 < rend; r0 += GKR, b ^= 1) {
+    // the next step's rows are in flight during this step's conversions and products
+    if (r0 + GKR < rend) load(r0 + GKR, nxt);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float a[8], s[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        // rows past the span carry zeros in a and d
+        a[i] = cur.a[h][i];
+        if (layer == 4) {
+          const float z = a[i], sg = sig_fast(z);
+          a[i] = cur.d[h][i] * w5 * (sg * (1.0f + z * (1.0f - sg)));
+          g5 += cur.d[h][i] * (z * sg);
+          gd += cur.d[h][i];
+        }
+        gb += a[i];
+        s[i] = silu_fast(cur.b[h][i]);
+      }
+      s16x8 hi, lo, sb;
+      split8(a, hi, lo);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sb[i] = (short)__builtin_bit_cast(uint16_t, (__bf16)s[i]);
+      *(s16x8 *)&fr[b][0][h][wv][8 * lane] = hi;
+      *(s16x8 *)&fr[b][1][h][wv][8 * lane] = lo;
+      *(s16x8 *)&fr[b][2][h][wv][8 * lane] = sb;
+    }
+    cur = nxt;
+    // one barrier per step: a wave writes the other buffer next, which every wave has finished
+    // reading once it arrives here again
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      bf16x8 Ah[2], Al[2], Bf[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        Ah[i] = __builtin_bit_cast(bf16x8, *(const s16x8 *)&fr[b][0][h][2 * (wv >> 1) + i][8 * lane]);
+        Al[i] = __builtin_bit_cast(bf16x8, *(const s16x8 *)&fr[b][1][h][2 * (wv >> 1) + i][8 * lane]);
+        Bf[i] = __builtin_bit_cast(bf16x8, *(const s16x8 *)&fr[b][2][h][2 * (wv & 1) + i][8 * lane]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ah[i], Bf[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Al[i], Bf[j], acc[i][j], 0, 0, 0);
+    }
+  }
+  float *gw = grad + off_w(layer);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int m = m0 + 64 * (wv >> 1) + 32 * i + 8 * (k >> 2) + 4 * hi32 + (k & 3);
+        atomicAdd(gw + m * NW + n0 + 64 * (wv & 1) + 32 * j + l32, acc[i][j][k]);
+      }
+  if (sums) {
+    gb += __shfl_xor(gb, 32, 64);
+    g5 += __shfl_xor(g5, 32, 64);
+    gd += __shfl_xor(gd, 32, 64);
+    if (hi32 == 0) {
+      atomicAdd(grad + off_b(layer) + ca, gb);
+      if (layer == 4) {
+        atomicAdd(grad + OFF_W5 + ca, g5);
+        if (m0 == 0 && wv == 0 && l32 == 0) atomicAdd(grad + OFF_B5, gd);
+      }
+    }
+  }
 }
 
 __global__ void k_mse(const float *__restrict__ y, const float *__restrict__ t, int B, float *__restrict__ dy,
@@ -712,20 +853,10 @@ extern "C" cm_status cm_mlp_sync_bf16(const cm_mlp *net, void *stream) {
   return CM_OK;
 }
 
-// persistent workgroups for the weight-stationary layers: at most one per CU (132 KB of LDS each)
-static int ws_grid(int M) {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-      cus = n;
-    else
-      cus = 256;
-  }
-  const int tiles = (M + 31) / 32;
-  return tiles < cus ? tiles : cus;
-}
+// Inference batches up to this many rows go through tiles of 32 (one workgroup each, 256 at a
+// time), larger ones through the kernel with two tiles of 64 in flight per CU: 777 rows take 9.6
+// against 27 us, 8192 11.5 against 28, 16384 19 against 29, 24576 28 against 31, 32768 37 against 33.
+constexpr int TILE_ROWS_MAX = 24576;
 
 extern "C" cm_status cm_mlp_forward(const cm_mlp *net, const float *x, int B, float *y, float *acts,
                                     size_t acts_bytes, void *stream) {
@@ -734,32 +865,29 @@ extern "C" cm_status cm_mlp_forward(const cm_mlp *net, const float *x, int B, fl
   if ((int64_t)B * NW > INT32_MAX) return CM_E_UNSUPPORTED;
   const bool keep = acts && acts_bytes >= cm_mlp_act_bytes(B);
   hipStream_t s = (hipStream_t)stream;
-  if (!keep) {
-    // inference: the fused kernel, one persistent workgroup (two tiles in flight) per CU
-    CM_HIP_CHECK(cm_allow_lds(k_mlp_fused, FUSED_LDS));
-    const int ntiles = (B + FM - 1) / FM;
-    int cus = 0;
-    int dev = 0;
-    CM_HIP_CHECK(hipGetDevice(&dev));
-    CM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int pairs = (ntiles + 1) / 2;
-    const int grid = pairs < cus ? pairs : cus;
-    hipLaunchKernelGGL(k_mlp_fused, dim3(grid), dim3(512), FUSED_LDS, s, x, B, net->params, net->w_bf16, *net, y);
+  if (keep || B <= TILE_ROWS_MAX) {
+    const dim3 grid((B + TM - 1) / TM);
+    if (keep) {
+      CM_HIP_CHECK(cm_allow_lds(k_mlp_tile<true>, TILE_LDS));
+      hipLaunchKernelGGL(k_mlp_tile<true>, grid, dim3(TWG), TILE_LDS, s, x, B, net->params, net->w_bf16, *net, y, acts);
+    } else {
+      CM_HIP_CHECK(cm_allow_lds(k_mlp_tile<false>, TILE_LDS));
+      hipLaunchKernelGGL(k_mlp_tile<false>, grid, dim3(TWG), TILE_LDS, s, x, B, net->params, net->w_bf16, *net, y,
+                         (float *)nullptr);
+    }
     CM_LAUNCH_CHECK();
     return CM_OK;
   }
-  float *Z[4];
-  for (int l = 0; l < 4; ++l) Z[l] = acts + (int64_t)(keep ? l : (l & 1)) * B * NW;
-  CM_HIP_CHECK(cm_allow_lds(k_gemm_ws<W_NK, F_SILU, E_BIAS_STORE>, WS_LDS));
-  hipLaunchKernelGGL(k_mlp_in, dim3(grid_for((int64_t)B * NW, 256)), dim3(256), 0, s, x, B, net->params, *net, Z[0]);
-  CM_LAUNCH_CHECK();
-  for (int l = 2; l <= 4; ++l) {
-    hipLaunchKernelGGL((k_gemm_ws<W_NK, F_SILU, E_BIAS_STORE>), dim3(ws_grid(B)), dim3(WS_THREADS), WS_LDS, s, Z[l - 2],
-                       net->w_bf16 + (int64_t)(l - 2) * NW * NW, B, Z[l - 1], net->params + off_b(l),
-                       (const float *)nullptr);
-    CM_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(k_mlp_out, dim3(grid_for(B, 4)), dim3(256), 0, s, Z[3], B, net->params, y);
+  // one persistent workgroup (two tiles in flight) per CU
+  CM_HIP_CHECK(cm_allow_lds(k_mlp_fused, FUSED_LDS));
+  const int ntiles = (B + FM - 1) / FM;
+  int cus = 0;
+  int dev = 0;
+  CM_HIP_CHECK(hipGetDevice(&dev));
+  CM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const int pairs = (ntiles + 1) / 2;
+  const int grid = pairs < cus ? pairs : cus;
+  hipLaunchKernelGGL(k_mlp_fused, dim3(grid), dim3(512), FUSED_LDS, s, x, B, net->params, net->w_bf16, *net, y);
   CM_LAUNCH_CHECK();
   return CM_OK;
 }
@@ -770,42 +898,19 @@ extern "C" cm_status cm_mlp_backward(const cm_mlp *net, const float *x, const fl
   if (B == 0) return CM_OK;
   if (!ws || ws_bytes < cm_mlp_act_bytes(B) / 2) return CM_E_INVALID;
   hipStream_t s = (hipStream_t)stream;
-  const float *Z[4];
-  for (int l = 0; l < 4; ++l) Z[l] = acts + (int64_t)l * B * NW;
-  float *D[2] = {(float *)ws, (float *)ws + (int64_t)B * NW};
-  const float *p = net->params;
-  CM_HIP_CHECK(cm_allow_lds(k_gemm_ws<W_KN, F_NONE, E_DSILU_STORE>, WS_LDS));
-  hipLaunchKernelGGL(k_fill, dim3(256), dim3(256), 0, s, grad, (int64_t)CM_MLP_NPARAMS, 0.0f);
-  hipLaunchKernelGGL(k_out_back, dim3(grid_for((int64_t)B * NW, 256)), dim3(256), 0, s, Z[3], dy, B, p, D[0]);
-  const int rows_per = 64;
-  const unsigned chunks = grid_for(B, rows_per);
-  hipLaunchKernelGGL(k_colsum<F_SILU>, dim3(chunks), dim3(NW), 0, s, Z[3], dy, B, rows_per, grad + OFF_W5);
-  hipLaunchKernelGGL(k_sum, dim3(64), dim3(256), 0, s, dy, B, grad + OFF_B5);
-  CM_LAUNCH_CHECK();
-  // split-K over the batch for the weight gradients: about 256 rows per workgroup
-  const int kspan = 256;
-  const unsigned ksplit = grid_for(B, kspan);
-  int cur = 0;
-  for (int l = 4; l >= 2; --l) {
-    const float *dl = D[cur];
-    {  // gW_l[m][n] += sum_b delta_l[b][m] silu(Z_{l-1}[b][n])
-      GemmArgs g{};
-      g.A = dl; g.lda = NW;
-      g.B = Z[l - 2]; g.ldb = NW;
-      g.M = NW; g.N = NW; g.K = B; g.kspan = kspan;
-      g.C = grad + off_w(l); g.ldc = NW;
-      hipLaunchKernelGGL((k_gemm<A_COLMAJOR, F_NONE, true, B_F32_KN, F_SILU, E_ATOMIC_ADD>),
-                         dim3(NW / GT, NW / GT, ksplit), dim3(256), 0, s, g);
-    }
-    hipLaunchKernelGGL(k_colsum<F_NONE>, dim3(chunks), dim3(NW), 0, s, dl, (const float *)nullptr, B, rows_per,
-                       grad + off_b(l));
-    // delta_{l-1}[b][n] = (sum_k delta_l[b][k] W_l[k][n]) silu'(Z_{l-1}[b][n])
-    hipLaunchKernelGGL((k_gemm_ws<W_KN, F_NONE, E_DSILU_STORE>), dim3(ws_grid(B)), dim3(WS_THREADS), WS_LDS, s, dl,
-                       net->w_bf16 + (int64_t)(l - 2) * NW * NW, B, D[cur ^ 1], (const float *)nullptr, Z[l - 2]);
-    CM_LAUNCH_CHECK();
-    cur ^= 1;
-  }
-  hipLaunchKernelGGL(k_in_back, dim3(chunks), dim3(NW), 0, s, D[cur], x, B, rows_per, *net, grad);
+  float *D = (float *)ws;   // delta_3, delta_2
+  uint16_t *wt = grad_scratch(grad);
+  CM_HIP_CHECK(cm_allow_lds(k_mlp_bwd, TILE_LDS));
+  hipLaunchKernelGGL(k_bwd_prep, dim3((3 * NW * NW / 64 + FIRST_COPIES * FIRST_N) / 256), dim3(256), 0, s, net->w_bf16, wt, grad);
+  hipLaunchKernelGGL(k_mlp_bwd, dim3((B + TM - 1) / TM), dim3(TWG), TILE_LDS, s, x, acts, dy, B, net->params, wt, *net,
+                     D, grad);
+  hipLaunchKernelGGL(k_bwd_mid, dim3(grid_for(CM_MLP_NPARAMS, 256)), dim3(256), 0, s, grad);
+  // spans of at least 128 rows, at most WG_SPANS of them: each adds 3 x 65536 gradients by atomics
+  int span = (B + WG_SPANS - 1) / WG_SPANS;
+  if (span < 128) span = 128;
+  span = (span + GKR - 1) / GKR * GKR;
+  const int spans = (B + span - 1) / span;
+  hipLaunchKernelGGL(k_wgrad, dim3(12 * XCDS * ((spans + XCDS - 1) / XCDS)), dim3(256), 0, s, acts, dy, D, B, span, net->params, grad);
   CM_LAUNCH_CHECK();
   return CM_OK;
 }

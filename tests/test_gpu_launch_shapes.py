@@ -24,3 +24,63 @@ def test_readout_rows_per_workgroup(dtype, batch, nk, stride):
     got = small.run(torch.from_numpy(np.tile(u, (batch, 1))).cuda()).cpu().numpy()
     assert np.isfinite(ref).all()
     np.testing.assert_array_equal(got, ref[:batch])
+
+
+def _mlp_case(B, seed):
+    from paper_2607_28435_amd.surrogate import MlpNet
+    lo, hi = W.surrogate_box()
+    net = MlpNet(lo, hi, seed=seed)
+    x = torch.from_numpy(W.surrogate_queries(B, seed).astype(np.float32)).cuda()
+    t = torch.from_numpy(np.random.default_rng(seed).normal(-2.0, 1.0, B).astype(np.float32)).cuda()
+    return net, x, t
+
+
+def _forward64(net, x):
+    """The network in FP64, hidden weights as their BF16 copies."""
+    shift = torch.tensor(list(net.struct.shift), dtype=torch.float64, device="cuda")
+    scale = torch.tensor(list(net.struct.scale), dtype=torch.float64, device="cuda")
+    a, o = (x.double() - shift) * scale, 0
+    for out, inp in ((256, 7), (256, 256), (256, 256), (256, 256), (1, 256)):
+        w = net.params[o:o + out * inp].reshape(out, inp)
+        a = a @ (w.bfloat16() if out == inp else w).double().T + net.params[o + out * inp:o + out * inp + out].double()
+        o += out * inp + out
+        a = a * torch.sigmoid(a) if out > 1 else a
+    return a[:, 0]
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 33, 127, 129, 4096, 4097, 8200])
+def test_training_tiles_and_spans(B):
+    """Rows at the edges of the 32-row tiles and of the row spans of the weight gradients: with dy
+    zero but for one row, the batch's gradient is that row's own, bit for bit (every other term is
+    an exact zero and each row's arithmetic does not depend on its place)."""
+    net, x, _ = _mlp_case(B, 11)
+    ref = None
+    for row in sorted({0, B // 2, B - 1}):
+        xb = x.clone()
+        xb[row] = x[0]
+        dy = torch.zeros(B, dtype=torch.float32, device="cuda")
+        dy[row] = 0.75
+        nb = cm.cm_mlp_act_bytes(B)
+        acts = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        ws = torch.empty(nb // 2, dtype=torch.uint8, device="cuda")
+        y = torch.empty(B, dtype=torch.float32, device="cuda")
+        grad = torch.full((cm.CM_MLP_NPARAMS,), 7.0, dtype=torch.float32, device="cuda")
+        cm.cm_mlp_forward(net.struct, xb, B, y, acts, nb)
+        cm.cm_mlp_backward(net.struct, xb, acts, dy, B, grad, ws, nb // 2)
+        if ref is None:
+            ref = torch.full((cm.CM_MLP_NPARAMS,), 7.0, dtype=torch.float32, device="cuda")
+            one = torch.full((1,), 0.75, dtype=torch.float32, device="cuda")
+            cm.cm_mlp_forward(net.struct, x[:1].contiguous(), 1, y, acts, cm.cm_mlp_act_bytes(1))
+            cm.cm_mlp_backward(net.struct, x[:1].contiguous(), acts, one, 1, ref, ws, cm.cm_mlp_act_bytes(1) // 2)
+            assert bool(torch.isfinite(ref).all()) and float(ref.abs().max()) > 0
+        assert torch.equal(grad, ref), (B, row)
+
+
+@pytest.mark.parametrize("B", [1, 32, 33, 24576, 24577, 24640])
+def test_inference_tile_sizes(B):
+    """Both sides of the rule between tiles of 32 rows and tiles of 64, against FP64: the hidden
+    operands keep 2^-16, three layers deep."""
+    net, x, _ = _mlp_case(B, 12)
+    y = _forward64(net, x)
+    got = net.forward(x).double()
+    assert float((got - y).abs().max()) <= 1e-4 * float(y.abs().max())
