@@ -84,3 +84,25 @@ def test_inference_tile_sizes(B):
     y = _forward64(net, x)
     got = net.forward(x).double()
     assert float((got - y).abs().max()) <= 1e-4 * float(y.abs().max())
+
+
+@pytest.mark.parametrize("dtype", [cm.CM_C64, cm.CM_C128])
+@pytest.mark.parametrize("quad", ["simpson1", "rect2"])
+@pytest.mark.parametrize("n", [1, 2, 3, 6, 11, 14, 15, 16, 19, 20, 21, 24])
+def test_dense_chosen_strikes_and_groups(dtype, quad, n):
+    """Chosen strikes are priced from the stored transform and every strike in the last pass: the
+    same transform, so they agree to the rounding of the scale 2^z (two units in the last place
+    each), at both ends of the grid and about the middle, over the pass plans (one pass up to
+    n = 15 or 14, two, and the reverse order of the chosen strikes in a second instance). The plan
+    does not depend on the batch: instances of a group agree bit for bit."""
+    p = W.bs_simpson_n12().replace(n=n, quad=quad, eta=0.25 if n < 16 else 0.05, alpha=1.5)
+    M = 2 ** n
+    u = np.unique(np.clip(np.concatenate([np.arange(5), M // 2 + np.arange(-5, 5), M - 1 - np.arange(5)]), 0, M - 1))
+    every, st = cm.dense_prices([p, p], dtype)
+    chosen, st2 = cm.dense_prices([p, p], dtype, torch.from_numpy(np.stack([u, u[::-1].copy()])).cuda())
+    assert int(st.abs().sum()) == 0 and int(st2.abs().sum()) == 0
+    assert torch.equal(torch.nan_to_num(every[0]), torch.nan_to_num(every[1]))
+    chosen = chosen.cpu().numpy()
+    every = every[0].cpu().numpy()
+    np.testing.assert_array_equal(chosen[1], chosen[0][::-1])
+    np.testing.assert_allclose(chosen[0], every[u], rtol=4 * np.finfo(every.dtype).eps, atol=np.finfo(every.dtype).tiny)
