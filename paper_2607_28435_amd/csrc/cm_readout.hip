@@ -93,11 +93,12 @@ template <> constexpr int rd_lds<double2>() { return 64 * 1024; }
 constexpr int TB_LO = 5, TB_H = 12, TB_K = 2;
 constexpr int TB_MID = 1 << (TB_H - TB_LO);
 // A block of RD_WG RD_SPT strikes decides between tree and plain contraction as a whole (the
-// two add in different orders). Its strikes go to one workgroup when the blocks fill the chip,
-// else to several, of four rows of RD_WG strikes or of one: one instance's 4096 strikes on one
-// workgroup left 255 CUs idle (n = 30 in FP64, 4096 strikes spread over the window: 644 ->
-// 66 us), and 256 instances of 513 strikes took their three rows one after the other.
-constexpr int RD_FILL = 512;
+// two add in different orders). Its strikes go to one workgroup, or to several of four rows of
+// RD_WG strikes or of one while that leaves at most one workgroup per CU: one instance's 4096
+// strikes on one workgroup left 255 CUs idle (n = 30 in FP64, 4096 strikes spread over the window:
+// 644 -> 66 us). Beyond one per CU the workgroups' own tree set-up, which each repeats, costs
+// more than the rows it saves (28 instances x 3992 strikes: 36 us slower in 448 workgroups).
+constexpr int RD_FILL = 256;
 
 // Contracts one strike: v <- Y_l[:, bit_l, :] v from l = n-1 down to 0; returns y_u.
 // Core l starts at base + off(l) and holds [rk[l]][2][rk[l+1]] values.
@@ -436,7 +437,7 @@ static cm_status readout(const cm_tt_batch *y, const cm_problem *prob, const int
   const int blocks = (nk + RD_WG * RD_SPT - 1) / (RD_WG * RD_SPT);
   const int64_t wgs = (int64_t)blocks * y->batch;
   const int used = blocks > 1 ? RD_SPT : (nk + RD_WG - 1) / RD_WG;   // rows of a block that hold strikes
-  const int rows = wgs >= RD_FILL ? RD_SPT : wgs * ((used + 3) / 4) >= RD_FILL ? 4 : 1;
+  const int rows = wgs * used <= RD_FILL ? 1 : wgs * ((used + 3) / 4) <= RD_FILL ? 4 : RD_SPT;
   const int parts = (used + rows - 1) / rows;
   const dim3 grid((unsigned)blocks * parts, (unsigned)y->batch);
   const int cap = y->cap_rank;
