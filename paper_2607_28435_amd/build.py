@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libcm.so")
 OBJ = os.path.join(ROOT, "_build", "obj")
 
-SOURCES = ["cm_abi.cpp", "cm_mpo.hip", "cm_qtt.hip", "cm_zipup.hip", "cm_round.hip", "cm_readout.hip",
+SOURCES = ["cm_abi.cpp", "cm_mpo.hip", "cm_qtt.hip", "cm_zipup.hip", "cm_round.hip", "cm_sweep_wide.hip", "cm_readout.hip",
            "cm_fft.hip", "cm_mlp.hip", "cm_sample.hip"]
 
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")

@@ -110,6 +110,15 @@ __host__ __device__ __forceinline__ double frac2(double hi, double lo) {
   return f;
 }
 
+// Batches of complex128 trains up to this size take the rounding sweeps on four waves per train
+// (cm_sweep_wide.hip): two trains a CU, which the one-wave kernels leave to the latency of one
+// sweep (256 Variance Gamma trains, n = 20: build 2.27 -> 1.56 ms, rounding 1.24 -> 1.04 ms; at 1024
+// Heston trains the two measure the same to a tenth, and 4096 of n = 24 would go from 2.1 + 2.0 to
+// 5.6 + 5.4 ms). Complex64 trains stay on one wave at every size: the sums of the two run in
+// different orders, and rounding the stored cores to FP32 turns a different last bit into a
+// difference of 1e-7 in a price.
+constexpr int WIDE_BATCH = 512;
+
 // Allows a kernel to take more than the default dynamic LDS (gfx950 has 160 KB per CU).
 template <typename K>
 static inline hipError_t cm_allow_lds(K kernel, size_t bytes) {

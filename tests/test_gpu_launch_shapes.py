@@ -14,12 +14,12 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("batch,nk,stride", [(1, 4096, 1), (1, 5000, 7), (3, 513, 1), (160, 1100, 3), (2, 1, 1)])
 def test_readout_rows_per_workgroup(dtype, batch, nk, stride):
     """Small read-outs give a workgroup one or four rows of 256 strikes of a block instead of all
-    sixteen; every price equals, bit for bit, the one of a batch of 600 that takes whole blocks."""
+    sixteen; every price equals, bit for bit, the one of a batch of 300 that takes whole blocks."""
     n = 18
     probs = W.heston_batch(4, seed=5, n=n)
-    big = cm.SfftPricer([probs[i % 4] for i in range(600)], dtype, tol=1e-8, cap=32)
+    big = cm.SfftPricer([probs[i % 4] for i in range(300)], dtype, tol=1e-8, cap=32)
     u = (2 ** (n - 1) - stride * (nk // 2) + stride * np.arange(nk, dtype=np.int64))
-    ref = big.run(torch.from_numpy(np.tile(u, (600, 1))).cuda()).cpu().numpy()
+    ref = big.run(torch.from_numpy(np.tile(u, (300, 1))).cuda()).cpu().numpy()
     small = cm.SfftPricer([probs[i % 4] for i in range(batch)], dtype, tol=1e-8, cap=32)
     got = small.run(torch.from_numpy(np.tile(u, (batch, 1))).cuda()).cpu().numpy()
     assert np.isfinite(ref).all()
@@ -106,3 +106,24 @@ def test_dense_chosen_strikes_and_groups(dtype, quad, n):
     every = every[0].cpu().numpy()
     np.testing.assert_array_equal(chosen[1], chosen[0][::-1])
     np.testing.assert_allclose(chosen[0], every[u], rtol=4 * np.finfo(every.dtype).eps, atol=np.finfo(every.dtype).tiny)
+
+
+@pytest.mark.parametrize("n", [1, 2, 5, 14, 20])
+def test_wide_and_one_wave_sweeps(n):
+    """Complex128 batches of 512 take the rounding sweeps on four waves per train, of 513 on one: the
+    same trains to the order of the FP64 sums. At tolerance 1e-10 each side's prices in the window
+    0.5 <= K/S0 <= 1.5 are within a few times 1e-10 S0 of the grid's own (the undamping there
+    is below 3^1.5), so the two lie within 1e-9 S0 of each other."""
+    probs = W.vg_batch(6, n=n) if n > 5 else W.bs_batch(6, n=n)
+    got, codes = [], []
+    for batch in (512, 513):
+        pr = cm.SfftPricer([probs[i % 6] for i in range(batch)], cm.CM_C128, tol=1e-10, cap=32)
+        u = [W.window_strided(p, 32) for p in probs]
+        k = min(len(v) for v in u)
+        s = np.stack([u[i % 6][:k] for i in range(batch)])
+        got.append(pr.run(torch.from_numpy(s).cuda()).cpu().numpy())
+        codes.append(np.stack([v[:512] for v in pr.statuses().values()]))
+        assert np.array_equal(got[-1][:6], got[-1][6:12], equal_nan=True)
+    np.testing.assert_array_equal(codes[0], codes[1])   # a five-point grid has instances the build refuses
+    ok = ~codes[0].any(axis=0)
+    assert ok.any() and np.abs(got[0] - got[1][:512])[ok].max() <= 1e-9 * probs[0].S0
