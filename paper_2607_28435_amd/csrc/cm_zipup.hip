@@ -14,7 +14,8 @@
 // runs in FP64. Sites with 2 chi <= 48 and w' r' <= 128 (the bulk of a pricing chain) keep
 // T in registers for the whole factorisation, each column on a group of two, four or eight
 // lanes (zip_site_pair); other sites stage their matrices in LDS when they fit, otherwise in the
-// workgroup's global slab.
+// workgroup's global slab. In large batches the small sites at the left end run in a kernel of
+// their own, one wave per instance (k_zip_left).
 #include <mutex>
 #include <type_traits>
 
@@ -645,12 +646,358 @@ __device__ __forceinline__ int zip_site_pair(char *arena, const SiteDims &sd, co
   return k;
 }
 
+// ---- left part of the chain, one wave per instance ---------------------------------------
+// The sites at the left end, where x is (nearly) separable, are small: 61 % of the sites of the
+// n = 24 Heston batch have at most 32 rows and 32 columns, the most frequent is 20 x 10. On four
+// waves most lanes hold no column and a pivot step is a chain of barrier, candidate exchange and
+// reductions. Here one 64-lane workgroup takes an instance through these sites: eight lanes per
+// column as in zip_site_pair<4, 8> (row 8 s + g in slot s of lane g), but columns q, q + 8, ... on
+// the group q, so every column's arithmetic, and with it every core, is that kernel's bit for
+// bit, the pivot search stays in the wave, and eight instances share a CU instead of three
+// (235 VGPRs; bounded to 168 it spills and measured 5.74 against 5.51 ms, with columns up to 16 at
+// 128 VGPRs 5.79). A site costs about 50 K cycles: staging 4, contraction 11, 8.9 pivot steps of
+// 3.2, Q 10; it is bound by the latency of these chains.
+// The carry into site l lives in y's core l until that site's output replaces it, so the wave
+// stops at the first site that is too large (or whose carry would not fit), leaves the site
+// and the status in y's last rank entry, and k_zipup goes on from there.
+constexpr int ZL_ROWS = 32, ZL_COLS = 32;   // largest site
+// Smallest capacity of y, whose cores hold the carries, and smallest batch for which the left part
+// runs apart. Alone on a CU its sites take longer than on four waves (one wave does all of a
+// site's work: 512 trains of n = 24 1.27 against 1.15 ms, 768 1.44 against 1.36); from four
+// trains a CU on it wins (1024 2.03 against 2.12 ms, 2048 2.99 against 3.31, 4096 5.80 against 6.48).
+constexpr int ZLEFT_CAP = 16, ZLEFT_BATCH = 1024;
+template <typename T> constexpr int zleft_lds() { return sizeof(T) == 8 ? 12 * 1024 : 20 * 1024; }
+// y.ranks[n] between the two kernels: -(site + 1) - 64 status (0: start from the first site)
+__device__ __forceinline__ int zleft_mark(int site, int code) { return -(site + 1) - 64 * code; }
+
+// Elements of y's core l at capacity: what every layout of cap_rank >= cap holds.
+__device__ __forceinline__ int64_t core_capacity(int l, int n, int cap) {
+  const int64_t rl = l < 6 ? (cap < (1 << l) ? cap : (1 << l)) : cap;
+  const int64_t rr = l == n - 1 ? 1 : l + 1 < 6 ? (cap < (2 << l) ? cap : (2 << l)) : cap;
+  return 2 * rl * rr;
+}
+
+template <typename T>
+__device__ __forceinline__ size_t left_stage_elems(const SiteDims &s) {   // carry, cores, two chunks of D
+  return (size_t)s.chi * s.w0 * s.r0 + (size_t)s.w0 * 4 * s.w1 + (size_t)s.r0 * 2 * s.r1 + (size_t)2 * 4 * s.w0 * 2 * s.r1;
+}
+
+// One site on one wave, NC columns per group of eight lanes (p <= 8 NC). Cin: the carry (pairs of
+// doubles, 8-byte aligned), Cout: the next one. Returns the rank.
+template <typename T, int NC>
+__device__ __forceinline__ int zip_site_wave(T *region, double2 *xcol, HouseRec *hrec, double2 *taus,
+                                             const SiteDims &sd, const T *__restrict__ Wl, const T *__restrict__ Al,
+                                             const double *Cin, bool first, double *Cout, T *Yout, double delta2,
+                                             int kcap, int *code) {
+  using A = acc_t<T>;
+  constexpr int G = 8, SMX = 4;
+  const int lane = threadIdx.x, gi = lane >> 3, g = lane & 7, u = g & 1, gh = g >> 1;
+  const int chi = sd.chi, w0 = sd.w0, w1 = sd.w1, r0 = sd.r0, r1 = sd.r1;
+  const int m = 2 * chi, p = w1 * r1;
+  T *Cl = region;
+  T *Wc = Cl + chi * w0 * r0;
+  T *Ac = Wc + w0 * 4 * w1;
+  T *Dch = Ac + r0 * 2 * r1;
+  double2 *V = (double2 *)region;   // reuses the region once T is in registers
+  const int dchunk = 4 * w0 * 2 * r1;
+  {
+    const int nc = chi * w0 * r0;
+    for (int e = lane; e < nc; e += 64) Cl[e] = A::from(first ? cmk(1.0, 0.0) : cmk(Cin[2 * e], Cin[2 * e + 1]));
+  }
+  {
+    const int nw = w0 * 4 * w1;
+    for (int e0 = lane; e0 < nw; e0 += 8 * 64) {   // eight loads in flight
+      T v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = Wl[e0 + 64 * q < nw ? e0 + 64 * q : 0];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (e0 + 64 * q < nw) Wc[e0 + 64 * q] = v[q];
+    }
+  }
+  for (int e = lane; e < r0 * 2 * r1; e += 64) Ac[e] = Al[e];
+  double2 t[NC][SMX];
+  bool act[NC];
+  int wp[NC], rp[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const int c = gi + 8 * j;
+    act[j] = c < p;
+    wp[j] = act[j] ? la::divmod_small(c, r1, rp[j]) : (rp[j] = 0);
+#pragma unroll
+    for (int sl = 0; sl < SMX; ++sl) t[j][sl] = cmk(0.0, 0.0);
+  }
+#pragma unroll
+  for (int ch0 = 0; ch0 < SMX * G / 2; ch0 += 4) {
+    if (ch0 < chi) {
+      T *Db = Dch + ((ch0 / 4) & 1) * dchunk;
+      __syncthreads();
+      for (int e = lane; e < dchunk; e += 64) {
+        int pr, ww;
+        const int row = la::divmod_small(e, 2 * r1, pr);
+        const int cc = la::divmod_small(row, w0, ww);
+        const int j = pr >= r1 ? 1 : 0, rpp = pr - j * r1;
+        typename A::type acc = A::zero();
+        if (ch0 + cc < chi) {
+          const T *crow = Cl + ((ch0 + cc) * w0 + ww) * r0;
+          for (int r = 0; r < r0; ++r) A::fma_(acc, crow[r], Ac[(r * 2 + j) * r1 + rpp]);
+        }
+        Db[e] = acc;
+      }
+      __syncthreads();
+      typename A::type acc[2][NC];
+#pragma unroll
+      for (int j = 0; j < NC; ++j) acc[0][j] = acc[1][j] = A::zero();
+      const T *dg = Db + gh * w0 * 2 * r1;
+      for (int ww = 0; ww < w0; ++ww)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const T *wr = Wc + (ww * 4 + 2 * u + b) * w1, *dr = dg + (ww * 2 + b) * r1;
+#pragma unroll
+          for (int j = 0; j < NC; ++j) A::fma_(acc[b][j], dr[rp[j]], wr[wp[j]]);
+        }
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        if (act[j] && ch0 + gh < chi) t[j][ch0 / 4] = A::to(A::add(acc[0][j], acc[1][j]));
+    }
+  }
+  __syncthreads();   // the region now holds V
+  double nrm[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    double nz[2] = {0.0, 0.0};
+#pragma unroll
+    for (int sl = 0; sl < SMX; ++sl) nz[sl & 1] += cabs2(t[j][sl]);
+    nrm[j] = nz[0] + nz[1];
+  }
+  la::grp_sum_n(nrm, G);
+  const int kmax = m < p ? m : p;
+  int i = 0;
+  while (true) {
+    // pivot: the largest key over this lane's columns, then over the wave's groups
+    unsigned long long key = 0ull;
+    double tail = 0.0;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const unsigned long long kj = act[j] ? pivot_key(nrm[j], gi + 8 * j) : 0ull;
+      key = kj > key ? kj : key;
+      tail += act[j] ? nrm[j] : 0.0;
+    }
+    wave_keymax_sum_uni<G>(key, tail);
+    const int pc = uni_i(key_col(key));
+    if (!(tail == tail) || isinf(tail)) {
+      if (lane == 0 && *code == CM_OK) *code = CM_E_NONFINITE;
+      break;
+    }
+    if (i >= kmax || (i >= 1 && tail <= delta2)) break;
+    if (i == kcap) {
+      if (lane == 0 && *code == CM_OK) *code = CM_E_RANKCAP;
+      break;
+    }
+    const int js = i / G, jw = pc >> 3;   // slots shifted so far; the pivot's place in its group
+    if (gi == (pc & 7)) {
+      double2 x[SMX];
+      double n2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        if (j == jw) {   // uniform
+          n2 = nrm[j];
+#pragma unroll
+          for (int sl = 0; sl < SMX; ++sl) x[sl] = t[j][sl];
+        }
+      const int r0w = G * js + g;
+      double2 v0 = x[0];
+      if (r0w < i) v0 = cmk(0.0, 0.0);
+      if (r0w == i) {
+        const House H = householder(n2, x[0]);
+        v0 = H.am;
+        hrec->wf = cscale(cconj(H.tau), cabs2(H.scal));
+        hrec->tau = H.tau;
+        hrec->scal = H.scal;
+        hrec->beta = H.beta;
+      }
+      xcol[g] = v0;
+#pragma unroll
+      for (int sl = 1; sl < SMX; ++sl) xcol[G * sl + g] = x[sl];
+    }
+    __syncthreads();
+    const double2 wf = hrec->wf, scal = hrec->scal;
+    const double beta = hrec->beta;
+    double2 x[SMX];
+#pragma unroll
+    for (int sl = 0; sl < SMX; ++sl) x[sl] = xcol[G * sl + g];
+    if (lane == 0) taus[i] = hrec->tau;
+    // reflector i for the Q accumulation
+    if (lane < ZL_ROWS) {
+      double2 v = cmk(0.0, 0.0);
+      if (lane == i) v = cmk(1.0, 0.0);
+      else if (lane > i && lane < m) v = cmul(xcol[lane - G * js], scal);
+      V[i * ZL_ROWS + lane] = v;
+    }
+    double pw[2 * NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      double2 pz[SMX];
+#pragma unroll
+      for (int e = 0; e < SMX; ++e) {
+        pz[e] = cmk(0.0, 0.0);
+        ccfma(pz[e], x[e], t[j][e]);
+      }
+      const double2 q = cadd(cadd(pz[0], pz[1]), cadd(pz[2], pz[3]));
+      pw[2 * j] = q.x;
+      pw[2 * j + 1] = q.y;
+    }
+    la::grp_sum_n(pw, G);
+    const bool skip0 = g <= i % G;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const double2 ws = cmul(wf, cmk(pw[2 * j], pw[2 * j + 1]));
+      double nz[2] = {0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < SMX; ++e) {
+        double2 y = t[j][e];
+        y.x = fma(x[e].y, ws.y, fma(-x[e].x, ws.x, y.x));
+        y.y = fma(-x[e].y, ws.x, fma(-x[e].x, ws.y, y.y));
+        t[j][e] = y;
+        if (e > 0 || !skip0) nz[e & 1] = fma(y.y, y.y, fma(y.x, y.x, nz[e & 1]));
+      }
+      nrm[j] = nz[0] + nz[1];
+      const int c = gi + 8 * j;
+      if (c < p && g == i % G) {
+        const double2 r = c == pc ? cmk(beta, 0.0) : act[j] ? t[j][0] : cmk(0.0, 0.0);
+        Cout[2 * (i * p + c)] = r.x;
+        Cout[2 * (i * p + c) + 1] = r.y;
+      }
+      if (i % G == G - 1) {
+#pragma unroll
+        for (int e = 0; e + 1 < SMX; ++e) t[j][e] = t[j][e + 1];
+        t[j][SMX - 1] = cmk(0.0, 0.0);
+      }
+      if (c == pc) act[j] = false;
+    }
+    la::grp_sum_n(nrm, G);
+    __syncthreads();   // xcol and hrec are written again
+    ++i;
+  }
+  const int k = i;
+  // Q = H_0 ... H_{k-1} [I_k; 0] on eight lanes per column (see zip_site_pair)
+  for (int c0 = gi; c0 < k; c0 += 16) {   // two columns of a group at a time
+    double2 qv[2][SMX];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int sl = 0; sl < SMX; ++sl) qv[q][sl] = cmk(8 * sl + g == c0 + 8 * q ? 1.0 : 0.0, 0.0);
+    double2 tc = taus[k - 1], vc[SMX], tn = cmk(0.0, 0.0), vn[SMX];
+#pragma unroll
+    for (int sl = 0; sl < SMX; ++sl) vc[sl] = V[(k - 1) * ZL_ROWS + 8 * sl + g];
+    for (int jj = k - 1; jj >= 0; --jj) {
+      if (jj > 0) {   // the next reflector is loaded while this one is applied
+        tn = taus[jj - 1];
+#pragma unroll
+        for (int sl = 0; sl < SMX; ++sl) vn[sl] = V[(jj - 1) * ZL_ROWS + 8 * sl + g];
+      }
+      if (tc.x != 0.0 || tc.y != 0.0) {
+        double d4[4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          double2 d = cmk(0.0, 0.0);
+#pragma unroll
+          for (int sl = 0; sl < SMX; ++sl)
+            if (8 * sl + 7 >= jj && 8 * sl < m) ccfma(d, vc[sl], qv[q][sl]);
+          d4[2 * q] = d.x;
+          d4[2 * q + 1] = d.y;
+        }
+        la::grp_sum_n(d4, 8);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const double2 wq = cmul(tc, cmk(d4[2 * q], d4[2 * q + 1]));
+#pragma unroll
+          for (int sl = 0; sl < SMX; ++sl)
+            if (8 * sl + 7 >= jj && 8 * sl < m) {
+              qv[q][sl].x = fma(vc[sl].y, wq.y, fma(-vc[sl].x, wq.x, qv[q][sl].x));
+              qv[q][sl].y = fma(-vc[sl].y, wq.x, fma(-vc[sl].x, wq.y, qv[q][sl].y));
+            }
+        }
+      }
+      tc = tn;
+#pragma unroll
+      for (int sl = 0; sl < SMX; ++sl) vc[sl] = vn[sl];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int sl = 0; sl < SMX; ++sl)
+        if (8 * sl + g < m && c0 + 8 * q < k) cstore<T>::st(Yout, (int64_t)(8 * sl + g) * k + c0 + 8 * q, qv[q][sl]);
+  }
+  __syncthreads();   // the region and the next carry
+  return k;
+}
+
 }  // namespace
+
+template <typename T>
+__global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTView x, TTView y, double tol, int cap) {
+  extern __shared__ __align__(16) char lds_arena[];
+  __shared__ double2 xcol[ZL_ROWS], taus[ZL_ROWS];
+  __shared__ HouseRec hrec;
+  __shared__ int code_sh;
+  const int lane = threadIdx.x, b = blockIdx.x;
+  const int n = x.n[b];
+  if (n < 1 || n > CM_MAX_N || n >= w_slots || y.n[b] != n || w.n[n] != n) return;   // k_zipup reports it
+  const int32_t *wr = w.rk(n), *xr = x.rk(b);
+  const T *Wc = (const T *)w.cores, *Xc = (const T *)x.cores;
+  T *Yc = (T *)y.cores;
+  double part = 0.0;
+  {
+    // ||x||^2 as k_zipup adds it: the entries in four groups of 64
+    const int cnt = 2 * xr[1];
+    double s2 = 0.0;
+    for (int v = 0; v < CM_WG / 64; ++v) {
+      double q = 0.0;
+      for (int e = 64 * v + lane; e < cnt; e += CM_WG) q += cabs2(cstore<T>::ld(Xc, x.coff(b, 0) + e));
+      s2 += la::grp_sum(q, 64);
+    }
+    part = s2;
+  }
+  const double delta2 = (n > 1) ? tol * tol * part / (double)(n - 1) : 0.0;
+  const int chicap = cap < ZCHI ? cap : ZCHI;
+  if (lane == 0) code_sh = CM_OK;
+  __syncthreads();
+  int chi = 1, l = 0;
+  for (; l < n - 1; ++l) {
+    SiteDims sd;
+    sd.chi = chi; sd.w0 = wr[l]; sd.w1 = wr[l + 1]; sd.r0 = xr[l]; sd.r1 = xr[l + 1];
+    const int m = 2 * chi, p = sd.w1 * sd.r1;
+    if (m > ZL_ROWS || p > ZL_COLS || sd.w0 > ZW || sd.w1 > ZW || sd.r0 > cap || sd.r1 > cap) break;
+    int kb = m < p ? m : p;
+    if (chicap < kb) kb = chicap;
+    // the staged operands, then the reflectors; the carry of at most kb rows in the next core
+    if (left_stage_elems<T>(sd) * sizeof(T) > (size_t)zleft_lds<T>() ||
+        sizeof(double2) * (size_t)kb * ZL_ROWS > (size_t)zleft_lds<T>() ||
+        sizeof(double2) * (int64_t)kb * p > (int64_t)sizeof(T) * core_capacity(l + 1, n, cap))
+      break;
+    const T *Wl = Wc + w.coff(n, l), *Al = Xc + x.coff(b, l);
+    T *Yout = Yc + y.coff(b, l);
+    const double *Cin = (const double *)Yout;
+    double *Cout = (double *)(Yc + y.coff(b, l + 1));
+    T *region = (T *)lds_arena;
+    const int k =
+        p <= 8    ? zip_site_wave<T, 1>(region, xcol, &hrec, taus, sd, Wl, Al, Cin, l == 0, Cout, Yout, delta2, chicap, &code_sh)
+        : p <= 16 ? zip_site_wave<T, 2>(region, xcol, &hrec, taus, sd, Wl, Al, Cin, l == 0, Cout, Yout, delta2, chicap, &code_sh)
+                  : zip_site_wave<T, 4>(region, xcol, &hrec, taus, sd, Wl, Al, Cin, l == 0, Cout, Yout, delta2, chicap, &code_sh);
+    if (lane == 0) y.rk(b)[l + 1] = k;
+    chi = k;
+  }
+  if (lane == 0) {
+    y.rk(b)[0] = 1;
+    y.rk(b)[n] = l > 0 ? zleft_mark(l, code_sh) : 0;
+  }
+}
 
 template <typename T>
 __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTView x, TTView y, double tol, int cap,
                                                  int batch, int32_t *__restrict__ status,
-                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap) {
+                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap, int left) {
   extern __shared__ __align__(16) char lds_arena[];
   __shared__ la::Sh sh;
   __shared__ int code_sh;
@@ -692,10 +1039,22 @@ __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTVie
       __syncthreads();
     }
     const double delta2 = (n > 1) ? tol * tol * xn2_sh / (double)(n - 1) : 0.0;
-    if (tid == 0) { C[0] = cmk(1.0, 0.0); y.rk(b)[0] = 1; }
+    // where k_zip_left stopped: its carry moves from y's core l0 to the slab
+    const int mark = left ? -y.rk(b)[n] : 0;
+    const int l0 = mark > 0 ? (mark - 1) & 63 : 0;
+    int chi = l0 > 0 ? y.rk(b)[l0] : 1;
+    if (l0 > 0) {
+      const double *cin = (const double *)(Yc + y.coff(b, l0));   // 8-byte aligned
+      const int cnt = chi * wr[l0] * xr[l0];
+      for (int e = tid; e < cnt; e += CM_WG) C[e] = cmk(cin[2 * e], cin[2 * e + 1]);
+      if (tid == 0) code_sh = (mark - 1) >> 6;
+    } else if (tid == 0) {
+      C[0] = cmk(1.0, 0.0);
+      y.rk(b)[0] = 1;
+    }
     __syncthreads();
-    int chi = 1;
-    for (int l = 0; l < n; ++l) {
+    if (left && tid == 0) y.rk(b)[n] = 1;   // a rank again, also for a chain that ends early
+    for (int l = l0; l < n; ++l) {
       SiteDims sd;
       sd.chi = chi; sd.w0 = wr[l]; sd.w1 = wr[l + 1]; sd.r0 = xr[l]; sd.r1 = xr[l + 1];
       const int m = 2 * chi, p = sd.w1 * sd.r1;
@@ -767,12 +1126,21 @@ static cm_status zip_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, doub
   TTView vw = tt_view(w_by_n), vx = tt_view(x), vy = tt_view(y);
   CM_HIP_CHECK(cm_allow_lds(k_zipup<float2>, zlds_bytes<float2>()));
   CM_HIP_CHECK(cm_allow_lds(k_zipup<double2>, zlds_bytes<double2>()));
-  if (x->dtype == CM_C64)
+  // the left part needs next cores that hold its carries
+  const int left = cap_rank >= ZLEFT_CAP && batch >= ZLEFT_BATCH;
+  if (x->dtype == CM_C64) {
+    if (left)
+      hipLaunchKernelGGL(k_zip_left<float2>, dim3(batch), dim3(64), zleft_lds<float2>(), s, vw, w_by_n->batch, vx, vy,
+                         tol, cap_rank);
     hipLaunchKernelGGL(k_zipup<float2>, dim3(slots), dim3(CM_WG), zlds_bytes<float2>(), s, vw, w_by_n->batch, vx, vy,
-                       tol, cap_rank, batch, status, (char *)ws, slab, mc);
-  else
+                       tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
+  } else {
+    if (left)
+      hipLaunchKernelGGL(k_zip_left<double2>, dim3(batch), dim3(64), zleft_lds<double2>(), s, vw, w_by_n->batch, vx,
+                         vy, tol, cap_rank);
     hipLaunchKernelGGL(k_zipup<double2>, dim3(slots), dim3(CM_WG), zlds_bytes<double2>(), s, vw, w_by_n->batch, vx,
-                       vy, tol, cap_rank, batch, status, (char *)ws, slab, mc);
+                       vy, tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
+  }
   CM_LAUNCH_CHECK();
   y->flags = CM_TT_LEFT_ORTHO;
   return CM_OK;

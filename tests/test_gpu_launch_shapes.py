@@ -127,3 +127,26 @@ def test_wide_and_one_wave_sweeps(n):
     np.testing.assert_array_equal(codes[0], codes[1])   # a five-point grid has instances the build refuses
     ok = ~codes[0].any(axis=0)
     assert ok.any() and np.abs(got[0] - got[1][:512])[ok].max() <= 1e-9 * probs[0].S0
+
+
+@pytest.mark.parametrize("model,n,cap", [("heston", 16, 32), ("heston", 24, 32), ("heston", 13, 16), ("heston", 20, 64),
+                                         ("bs", 1, 32), ("bs", 2, 32), ("bs", 3, 16), ("vg", 18, 24)])
+def test_zip_left_part(model, n, cap):
+    """Batches of 1024 run the left sites of the zip-up on one wave per instance, smaller ones on
+    four: the same arithmetic per column, so complex64 trains agree bit for bit, their ranks and
+    statuses too (a capacity of 16 also makes the wave hand over early)."""
+    probs = {"heston": lambda: W.heston_batch(8, seed=3, n=n), "bs": lambda: W.bs_batch(8, n=n),
+             "vg": lambda: W.vg_batch(8, n=n)}[model]()
+    u = np.stack([W.near_money(p, 64) for p in probs])
+    out = []
+    for batch in (8, 1024):
+        pr = cm.SfftPricer([probs[i % 8] for i in range(batch)], cm.CM_C64, tol=1e-8, cap=cap)
+        pr.build()
+        pr.apply()
+        ranks = pr.y.ranks[:, :n + 1].clone()
+        prices = pr.run(torch.from_numpy(np.tile(u, (batch // 8, 1))).cuda())
+        out.append((ranks, prices, pr.statuses()["apply"]))
+    (r0, p0, s0), (r1, p1, s1) = out
+    assert torch.equal(r0.repeat(128, 1), r1) and bool((r1[:, n] == 1).all())
+    assert torch.equal(torch.nan_to_num(p0.repeat(128, 1)), torch.nan_to_num(p1))
+    assert np.array_equal(np.tile(s0, 128), s1)
