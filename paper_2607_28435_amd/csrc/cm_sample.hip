@@ -12,11 +12,25 @@
 // precision of the train.
 //
 // k_envs: one workgroup per instance builds E_n, ..., E_0 in LDS and stores E_1..E_n and
-// the FP64 cores in the workspace, zero-padded to bond dimensions rounded up to multiples
-// of 4. k_sample: one lane per shot holding its prefix row in registers (sized by a
-// compile-time bound on the instance's largest bond); the products run over 4 x 4 blocks
-// of the padded operands, whose addresses are the same for every lane, so the operands
-// arrive through scalar loads and each block's loads are issued together.
+// the FP64 cores in the workspace, zero-padded to even bond dimensions (multiples of 4 in
+// trains with bonds above 16). k_sample: one lane per shot holding its prefix row in registers
+// (sized by a compile-time bound on the instance's largest bond); the products run over 4 x 4
+// blocks of the padded operands, 2 wide at the remainder, whose addresses are the same for
+// every lane, so the operands arrive through scalar loads and each block's loads are issued
+// together.
+//
+// k_sample is bound by the FP64 multiply-adds it executes and, with three waves a SIMD, by the
+// scalar loads between them; so what counts is how much of the work is padding and how far the
+// loads run ahead. Blocks of 4 made 1.43 times the work out of a bond of 10. Up to bonds of 16
+// the padding is to 2, bonds up to 12 have an instantiation that fits four waves, and the two
+// largest sizes of each have branch-free code. 512 Heston trains of n = 24 (bonds <= 10), 4096
+// shots: 2.53 -> 1.93 ms. 256 trains of n = 20 by their bond, 4096 shots, the whole call: 6:
+// 0.68 -> 0.51 ms, 8: 0.70 -> 0.71, 10: 1.64 -> 1.06, 12: 1.65 -> 1.31, 14: 2.54 -> 1.92,
+// 16: 2.57 -> 2.31. Above 16 the same blocks of 2 are 9 % slower than whole ones (24: 14.2 against
+// 12.7 ms; one wave a SIMD, and the remainder is a small part): those keep blocks of 4. Orthonormal
+// rows in place of the environments (a mass is then ||w||^2: a third of the work less) took
+// 1.60 ms here, but the factorisations 0.64 against k_envs' 0.11, and the masses' error against
+// extended precision is 2.6e-15 against 1.0e-15.
 #include "cm_internal.h"
 
 namespace {
@@ -31,11 +45,15 @@ __device__ __forceinline__ int max_bond_of(const int32_t *rk, int n) {
 }
 
 __host__ __device__ __forceinline__ int pad4(int r) { return (r + 3) & ~3; }
+// bonds up to PAD2_MAX are padded to multiples of 2, wider trains' to multiples of 4
+constexpr int PAD2_MAX = 16;
+__device__ __forceinline__ int pad_bond(int r, bool wide) { return wide ? pad4(r) : (r + 1) & ~1; }
 
 // Workspace slab of one instance (complex FP64 elements):
-//   E_l, l = 1..n:   at l * RS * RS, [p4(r_l)][p4(r_l)]
-//   Y_l, l = 0..n-1: at (n_max + 1) RS^2 + l * 2 RS^2, [p4(r_l)][2][p4(r_{l+1})]
-// with p4 = round up to a multiple of 4 and zeros in the padding.
+//   the largest bond, an int, at 0
+//   E_l, l = 1..n:   at l * RS * RS, [p(r_l)][p(r_l)]
+//   Y_l, l = 0..n-1: at (n_max + 1) RS^2 + l * 2 RS^2, [p(r_l)][2][p(r_{l+1})]
+// with p = pad_bond and zeros in the padding.
 template <typename T>
 __global__ __launch_bounds__(SMP_WG) void k_envs(TTView y, int RS, int n_max, int64_t inst_stride,
                                                  double2 *__restrict__ ws, double *__restrict__ norm2,
@@ -56,23 +74,26 @@ __global__ __launch_bounds__(SMP_WG) void k_envs(TTView y, int RS, int n_max, in
     return;
   }
   const int32_t *rk = y.rk(b);
-  if (max_bond_of(rk, n) > RS) {
+  const int rmax = max_bond_of(rk, n);
+  double2 *Eg = ws + (int64_t)b * inst_stride;
+  if (tid == 0) *(int32_t *)Eg = rmax;
+  if (rmax > RS) {
     if (tid == 0) {
       norm2[b] = NAN;
       set_status(status, b, CM_E_UNSUPPORTED);
     }
     return;
   }
-  double2 *Eg = ws + (int64_t)b * inst_stride;
   double2 *Yg = Eg + (int64_t)(n_max + 1) * RS * RS;
   const T *cores = (const T *)y.cores;
-  // E_n = [1], padded to 4 x 4
+  const bool wide = rmax > PAD2_MAX;
+  // E_n = [1], padded to at most 4 x 4
   for (int e = tid; e < 16; e += SMP_WG) Eg[(int64_t)n * RS * RS + e] = cmk(e == 0 ? 1.0 : 0.0, 0.0);
   if (tid == 0) Ea[0] = cmk(1.0, 0.0);
   __syncthreads();
   for (int l = n - 1; l >= 0; --l) {
     const int ra = rk[l], rb = rk[l + 1];
-    const int pa = pad4(ra), pb = pad4(rb);
+    const int pa = pad_bond(ra, wide), pb = pad_bond(rb, wide);
     const T *C = cores + y.coff(b, l);
     for (int e = tid; e < ra * 2 * rb; e += SMP_WG) Yd[e] = cstore<T>::ld(C, e);
     // padded FP64 copy of the core for the sampler
@@ -120,77 +141,111 @@ __global__ __launch_bounds__(SMP_WG) void k_envs(TTView y, int RS, int n_max, in
   }
 }
 
-// w <- v Y[:, bit, :] over 4 x 4 blocks of the padded core Y ([pa][2][pb], pa, pb <= RM).
-// Entries of v past the bond are zero, and so are the padded columns of Y.
-template <int RM>
-__device__ __forceinline__ void row_times_core(const double2 *v, const double2 *__restrict__ Y, int pa, int pb,
-                                               int bit, double2 *w) {
+// w <- v Y[:, bit, :] over blocks of the padded core Y (rows of ld, pb of them used; pa, pb <= RM).
+// Entries of v past the bond are zero, and so is Y's padding. WHOLE: pa and pb are multiples of 4;
+// else they are even and the last block of each is 2 wide where that is enough.
+template <int RM> constexpr bool WHOLE = RM > PAD2_MAX;
+
+template <int RA, int RB>
+__device__ __forceinline__ void block_product(const double2 *v, const double2 *__restrict__ Y, int ld, double2 *w) {
+  double2 yb[RA][RB];
 #pragma unroll
-  for (int c = 0; c < RM; ++c) w[c] = cmk(0.0, 0.0);
+  for (int i = 0; i < RA; ++i)
 #pragma unroll
-  for (int c4 = 0; c4 < RM; c4 += 4) {
-    if (c4 < pb) {
+    for (int j = 0; j < RB; ++j) yb[i][j] = Y[i * ld + j];
 #pragma unroll
-      for (int a4 = 0; a4 < RM; a4 += 4) {
-        if (a4 < pa) {
-          double2 yb[4][4];
+  for (int i = 0; i < RA; ++i)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < RB; ++j) cfma(w[j], v[i], yb[i][j]);
+}
+
+template <int RM, int RB>
+__device__ __forceinline__ void column_product(const double2 *v, const double2 *__restrict__ Y, int pa, int ld,
+                                               double2 *w) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) yb[i][j] = Y[((a4 + i) * 2 + bit) * pb + c4 + j];
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cfma(w[c4 + j], v[a4 + i], yb[i][j]);
-        }
-      }
-    }
+  for (int a = 0; a < RM; a += 4) {
+    if (a + 4 <= pa) block_product<4, RB>(v + a, Y + a * ld, ld, w);
+    else if (!WHOLE<RM> && a < pa) block_product<2, RB>(v + a, Y + a * ld, ld, w);
   }
 }
 
-// w E w^H for Hermitian E (padded [p][p], p <= RM) from its upper triangle, 4 x 4 blocks.
 template <int RM>
-__device__ __forceinline__ double quad_form(const double2 *w, const double2 *__restrict__ E, int p) {
-  double acc = 0.0;
+__device__ __forceinline__ void row_times_core(const double2 *v, const double2 *__restrict__ Y, int pa, int pb,
+                                               double2 *w) {
 #pragma unroll
-  for (int c4 = 0; c4 < RM; c4 += 4) {
-    if (c4 < p) {
-      // z_i = sum_{d > c4+i} conj(E[c4+i][d]) w[d]
-      double2 z[4];
+  for (int c = 0; c < RM; ++c) w[c] = cmk(0.0, 0.0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) z[i] = cmk(0.0, 0.0);
-      double diag[4];
+  for (int c = 0; c < RM; c += 4) {
+    if (c + 4 <= pb) column_product<RM, 4>(v, Y + c, pa, 2 * pb, w + c);
+    else if (!WHOLE<RM> && c < pb) column_product<RM, 2>(v, Y + c, pa, 2 * pb, w + c);
+  }
+}
+
+// w E w^H for Hermitian E (padded [p][p], p <= RM) from its upper triangle, by blocks.
+// z_i += sum_d conj(E[i][d]) w[d] over one block of CW rows and DW columns
+template <int CW, int DW>
+__device__ __forceinline__ void form_block(const double2 *w, const double2 *__restrict__ E, int p, double2 *z) {
+  double2 eb[CW][DW];
 #pragma unroll
-      for (int d4 = c4; d4 < RM; d4 += 4) {
-        if (d4 < p) {
-          double2 eb[4][4];
+  for (int i = 0; i < CW; ++i)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < DW; ++j) eb[i][j] = E[i * p + j];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (d4 > c4 || j >= i) eb[i][j] = E[(c4 + i) * p + d4 + j];
+  for (int i = 0; i < CW; ++i)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (d4 == c4) diag[i] = eb[i][i].x;
+    for (int j = 0; j < DW; ++j) ccfma(z[i], eb[i][j], w[j]);
+}
+
+// rows c .. c + CW - 1 of the form: w and E start at entry (c, c), `rest` entries from there on
+template <bool W, int MAXD, int CW>
+__device__ __forceinline__ void form_rows(const double2 *w, const double2 *__restrict__ E, int p, int rest,
+                                          double &acc) {
+  double2 z[CW], eb[CW][CW];   // the diagonal block, its upper triangle
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (d4 > c4 || j > i) ccfma(z[i], eb[i][j], w[d4 + j]);
-          }
-        }
-      }
+  for (int i = 0; i < CW; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double2 wc = w[c4 + i];
-        acc = fma(diag[i], cabs2(wc), acc);
-        acc = fma(2.0, wc.x * z[i].x + wc.y * z[i].y, acc);
-      }
+    for (int j = i; j < CW; ++j) eb[i][j] = E[i * p + j];
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    z[i] = cmk(0.0, 0.0);
+#pragma unroll
+    for (int j = i + 1; j < CW; ++j) ccfma(z[i], eb[i][j], w[j]);
+  }
+  if (CW == 4) {
+#pragma unroll
+    for (int d = 4; d < MAXD; d += 4) {
+      if (d + 4 <= rest) form_block<CW, 4>(w + d, E + d, p, z);
+      else if (!W && d < rest) form_block<CW, 2>(w + d, E + d, p, z);
     }
   }
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    acc = fma(eb[i][i].x, cabs2(w[i]), acc);
+    acc = fma(2.0, w[i].x * z[i].x + w[i].y * z[i].y, acc);
+  }
+}
+
+template <int RM, int C>
+__device__ __forceinline__ void form_from(const double2 *w, const double2 *__restrict__ E, int p, double &acc) {
+  if constexpr (C < RM) {
+    if (C + 4 <= p) form_rows<WHOLE<RM>, RM - C, 4>(w + C, E + C * p + C, p, p - C, acc);
+    else if (!WHOLE<RM> && C < p) form_rows<WHOLE<RM>, RM - C, 2>(w + C, E + C * p + C, p, p - C, acc);
+    form_from<RM, C + 4>(w, E, p, acc);
+  }
+}
+
+// one continuation: w <- v Y, returns its mass
+template <int RM>
+__device__ __forceinline__ double continuation(const double2 *v, const double2 *Y, const double2 *E, int pa, int pb,
+                                               double2 *w) {
+  double acc = 0.0;
+  row_times_core<RM>(v, Y, pa, pb, w);
+  form_from<RM, 0>(w, E, pb, acc);
   return acc;
 }
 
 template <int RM>
-__global__ __launch_bounds__(SMP_WG) void k_sample(TTView y, const double2 *__restrict__ ws, int RS, int n_max,
+__global__ __launch_bounds__(SMP_WG, RM <= 8 ? 4 : RM <= 12 ? 4 : RM <= 16 ? 3 : 1) void k_sample(TTView y, const double2 *__restrict__ ws, int RS, int n_max,
                                                    int64_t inst_stride, const double *__restrict__ norm2,
                                                    const double *__restrict__ uni, int ustride, int R,
                                                    int64_t *__restrict__ out, int rm_lo) {
@@ -205,7 +260,8 @@ __global__ __launch_bounds__(SMP_WG) void k_sample(TTView y, const double2 *__re
   const int32_t *rk = y.rk(b);
   // this instantiation serves instances whose largest bond lies in (rm_lo, RM]; the widest
   // one also writes -1 for instances above every bound
-  const int rmax = max_bond_of(rk, n);
+  const double2 *Eg = ws + (int64_t)b * inst_stride;
+  const int rmax = *(const int32_t *)Eg;
   if (rmax <= rm_lo) return;
   if (s >= R) return;
   const double q_all = norm2[b];
@@ -215,7 +271,6 @@ __global__ __launch_bounds__(SMP_WG) void k_sample(TTView y, const double2 *__re
   }
   // uniforms are bit-major, [batch][ustride][R]: level t of consecutive shots is contiguous
   const double *U = uni + (int64_t)b * ustride * R + s;
-  const double2 *Eg = ws + (int64_t)b * inst_stride;
   const double2 *Yg = Eg + (int64_t)(n_max + 1) * RS * RS;
   double2 v[RM], w[RM];
 #pragma unroll
@@ -224,18 +279,27 @@ __global__ __launch_bounds__(SMP_WG) void k_sample(TTView y, const double2 *__re
   double q = q_all;
   int64_t idx = 0;
   for (int t = 0; t < n; ++t) {
-    const int pa = pad4(rk[t]), pb = pad4(rk[t + 1]);
+    const int pa = pad_bond(rk[t], WHOLE<RM>), pb = pad_bond(rk[t + 1], WHOLE<RM>);
     const double ut = U[(int64_t)t * R];
     const double2 *Y = Yg + (int64_t)t * 2 * RS * RS;
     const double2 *E = Eg + (int64_t)(t + 1) * RS * RS;
-    row_times_core<RM>(v, Y, pa, pb, 0, w);
-    const double q0 = quad_form<RM>(w, E, pb);
-    const bool one = ut * q >= q0;
-    q = q0;
-    if (one) {
-      row_times_core<RM>(v, Y, pa, pb, 1, w);
-      q = quad_form<RM>(w, E, pb);
-      idx |= (int64_t)1 << t;
+    // up to 16 one copy of the products' code serves both bits, as the sizes that fill most of a
+    // chain (both bonds the largest or the next even one) have copies of their own: without
+    // branches between the blocks the scalar loads run ahead of the products. Lanes that keep bit 0
+    // sit out the second pass.
+    const double lim = ut * q;
+    bool more = true;
+#pragma unroll(RM > PAD2_MAX ? 2 : 1)
+    for (int bit = 0; bit < 2; ++bit) {
+      if (more) {
+        const double2 *Yb = Y + bit * pb;
+        if (RM <= PAD2_MAX && pa == RM - 2 && pb == RM - 2) q = continuation<RM>(v, Yb, E, RM - 2, RM - 2, w);
+        else if (RM <= PAD2_MAX && pa == RM && pb == RM) q = continuation<RM>(v, Yb, E, RM, RM, w);
+        else if (RM == 8 && pa == 4 && pb == 4) q = continuation<RM>(v, Yb, E, 4, 4, w);
+        else q = continuation<RM>(v, Yb, E, pa, pb, w);
+        if (bit) idx |= (int64_t)1 << t;
+        more = lim >= q;
+      }
     }
 #pragma unroll
     for (int a = 0; a < RM; ++a) v[a] = w[a];
@@ -288,7 +352,8 @@ extern "C" cm_status cm_sample_outcomes(const cm_tt_batch *y, const double *unif
   hipLaunchKernelGGL((k_sample<RM>), grid, dim3(SMP_WG), 0, s, v, slab, RS, nm, inst_stride, norm2, uniforms, us, R, \
                      out, LO)
   CM_SAMPLE_LAUNCH(8, 0);
-  if (y->cap_rank > 8) CM_SAMPLE_LAUNCH(16, 8);
+  if (y->cap_rank > 8) CM_SAMPLE_LAUNCH(12, 8);
+  if (y->cap_rank > 12) CM_SAMPLE_LAUNCH(16, 12);
   if (y->cap_rank > 16) CM_SAMPLE_LAUNCH(32, 16);
 #undef CM_SAMPLE_LAUNCH
   CM_LAUNCH_CHECK();

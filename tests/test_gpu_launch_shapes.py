@@ -150,3 +150,25 @@ def test_zip_left_part(model, n, cap):
     assert torch.equal(r0.repeat(128, 1), r1) and bool((r1[:, n] == 1).all())
     assert torch.equal(torch.nan_to_num(p0.repeat(128, 1)), torch.nan_to_num(p1))
     assert np.array_equal(np.tile(s0, 128), s1)
+
+
+# ------------------------------------------------------------------ sampler: padding and sizes
+
+@pytest.mark.parametrize("rmax,cap", [(1, 1), (2, 8), (3, 5), (6, 8), (7, 7), (9, 9), (10, 12), (11, 32), (13, 16),
+                                      (14, 32), (15, 15), (17, 20), (18, 32)])
+def test_sampler_bond_paddings(rmax, cap):
+    """Bonds on both sides of every padding and of every size the sampler has code of its own
+    for, in trains whose ends run through the smaller bonds: the outcomes are the oracle's for
+    the same uniforms. A decision may differ only where the oracle's own margin is below 1e-10:
+    the masses carry some n r^2 = 12 * 18^2 roundings of 1.1e-16, 4.4e-13."""
+    from test_gpu_observable import _check_samples, _probs_of_output_train, _random_trains, _sample, _uniforms
+    ns = [11, 12, 2, 7]
+    tt, host = _random_trains(ns, rmax, cm.CM_C128, cap, seed=500 + rmax)
+    R = 1100
+    U = _uniforms(len(ns), R, max(ns), seed=rmax)
+    got, norm2, st = _sample(tt, U)
+    assert np.all(st == cm.CM_OK), st
+    for b, n in enumerate(ns):
+        prob, nrm = _probs_of_output_train(host[b])
+        assert abs(norm2[b] - nrm) <= 1e-11 * nrm
+        _check_samples(prob, U[b, :, :n], got[b], margin_tol=1e-10, max_frac=0.0)
