@@ -566,10 +566,12 @@ FFT_SOURCES = ["paper_2607_28435_amd/csrc/cm_fft.hip", "paper_2607_28435_amd/csr
                "paper_2607_28435_amd/csrc/cm_tt.h", "paper_2607_28435_amd/csrc/cm_linalg.h",
                "paper_2607_28435_amd/csrc/cm_internal.h", "include/cm.h"]
 SAMPLE_SOURCES = ["paper_2607_28435_amd/csrc/cm_sample.hip", "paper_2607_28435_amd/csrc/cm_internal.h", "include/cm.h"]
-BUILD_SOURCES = ["paper_2607_28435_amd/csrc/cm_qtt.hip", "paper_2607_28435_amd/csrc/cm_cf.h",
+BUILD_SOURCES = ["paper_2607_28435_amd/csrc/cm_qtt.hip", "paper_2607_28435_amd/csrc/cm_qtt_round.h",
+                 "paper_2607_28435_amd/csrc/cm_cf.h",
                  "paper_2607_28435_amd/csrc/cm_tt.h", "paper_2607_28435_amd/csrc/cm_linalg.h",
                  "paper_2607_28435_amd/csrc/cm_internal.h", "include/cm.h"]
-ROUND_SOURCES = ["paper_2607_28435_amd/csrc/cm_round.hip", "paper_2607_28435_amd/csrc/cm_tt.h",
+ROUND_SOURCES = ["paper_2607_28435_amd/csrc/cm_round.hip", "paper_2607_28435_amd/csrc/cm_round_kernel.h",
+                 "paper_2607_28435_amd/csrc/cm_tt.h",
                  "paper_2607_28435_amd/csrc/cm_linalg.h", "paper_2607_28435_amd/csrc/cm_internal.h", "include/cm.h"]
 READ_SOURCES = ["paper_2607_28435_amd/csrc/cm_readout.hip", "paper_2607_28435_amd/csrc/cm_cf.h",
                 "paper_2607_28435_amd/csrc/cm_tt.h", "paper_2607_28435_amd/csrc/cm_linalg.h",
@@ -793,7 +795,8 @@ def main():
     dense_ms_ev = e0.elapsed_time(e1) / (reps * nd)
     M = 2 ** args.n
     dense_gps = 1.0 / dense_s
-    dense_bytes = 8 * M + (8 * M + 4 * M) if args.n > 14 else 4 * M   # pass-1 write, pass-2 read + price write
+    # half-length transform: pass-1 write, pass-2 read (M / 2 complex points) + price write
+    dense_bytes = 4 * M + (4 * M + 4 * M) if args.n > 15 else 4 * M
     dense_gbs = dense_bytes / (dense_ms_ev * 1e-3) / 1e9
     # the same grids four instances per launch group (a workspace sized for it): the pass
     # buffers (4 x 134 MB at n = 24) exceed the 256 MB Infinity Cache, so the intermediate
