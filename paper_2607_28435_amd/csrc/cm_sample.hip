@@ -87,8 +87,9 @@ __global__ __launch_bounds__(SMP_WG) void k_envs(TTView y, int RS, int n_max, in
   double2 *Yg = Eg + (int64_t)(n_max + 1) * RS * RS;
   const T *cores = (const T *)y.cores;
   const bool wide = rmax > PAD2_MAX;
-  // E_n = [1], padded to at most 4 x 4
-  for (int e = tid; e < 16; e += SMP_WG) Eg[(int64_t)n * RS * RS + e] = cmk(e == 0 ? 1.0 : 0.0, 0.0);
+  // E_n = [1], padded to at most 4 x 4 (a train of no cores has no level that reads it, and its
+  // place is the largest bond's)
+  for (int e = tid; e < 16 && n > 0; e += SMP_WG) Eg[(int64_t)n * RS * RS + e] = cmk(e == 0 ? 1.0 : 0.0, 0.0);
   if (tid == 0) Ea[0] = cmk(1.0, 0.0);
   __syncthreads();
   for (int l = n - 1; l >= 0; --l) {
