@@ -670,10 +670,10 @@ template <typename T> constexpr int zleft_lds() { return sizeof(T) == 8 ? 12 * 1
 // y.ranks[n] between the two kernels: -(site + 1) - 64 status (0: start from the first site)
 __device__ __forceinline__ int zleft_mark(int site, int code) { return -(site + 1) - 64 * code; }
 
-// Elements of y's core l at capacity: what every layout of cap_rank >= cap holds.
+// Elements of core l of a train of n cores as cm_tt_layout spaces them.
 __device__ __forceinline__ int64_t core_capacity(int l, int n, int cap) {
-  const int64_t rl = l < 6 ? (cap < (1 << l) ? cap : (1 << l)) : cap;
-  const int64_t rr = l == n - 1 ? 1 : l + 1 < 6 ? (cap < (2 << l) ? cap : (2 << l)) : cap;
+  const int64_t rl = l < 30 ? (cap < (1 << l) ? cap : (1 << l)) : cap;
+  const int64_t rr = l == n - 1 ? 1 : l + 1 < 30 ? (cap < (2 << l) ? cap : (2 << l)) : cap;
   return 2 * rl * rr;
 }
 
@@ -936,7 +936,8 @@ __device__ __forceinline__ int zip_site_wave(T *region, double2 *xcol, HouseRec 
 }  // namespace
 
 template <typename T>
-__global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTView x, TTView y, double tol, int cap) {
+__global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTView x, TTView y, double tol, int cap,
+                                                    int ycap) {
   extern __shared__ __align__(16) char lds_arena[];
   __shared__ double2 xcol[ZL_ROWS], taus[ZL_ROWS];
   __shared__ HouseRec hrec;
@@ -944,6 +945,14 @@ __global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTVie
   const int lane = threadIdx.x, b = blockIdx.x;
   const int n = x.n[b];
   if (n < 1 || n > CM_MAX_N || n >= w_slots || y.n[b] != n || w.n[n] != n) return;   // k_zipup reports it
+  // The carries live in y's cores beyond their ranks. Only cm_tt_layout's spacing says that the
+  // room between two offsets is the train's own (the last core's end is not seen, so it holds no
+  // carry): any other table leaves the whole chain to k_zipup.
+  const bool spaced = lane + 1 >= n || y.coff(b, lane + 1) - y.coff(b, lane) == core_capacity(lane, n, ycap);
+  if (!__all(spaced)) {
+    if (lane == 0) y.rk(b)[n] = 0;
+    return;
+  }
   const int32_t *wr = w.rk(n), *xr = x.rk(b);
   const T *Wc = (const T *)w.cores, *Xc = (const T *)x.cores;
   T *Yc = (T *)y.cores;
@@ -964,7 +973,7 @@ __global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTVie
   if (lane == 0) code_sh = CM_OK;
   __syncthreads();
   int chi = 1, l = 0;
-  for (; l < n - 1; ++l) {
+  for (; l < n - 2; ++l) {
     SiteDims sd;
     sd.chi = chi; sd.w0 = wr[l]; sd.w1 = wr[l + 1]; sd.r0 = xr[l]; sd.r1 = xr[l + 1];
     const int m = 2 * chi, p = sd.w1 * sd.r1;
@@ -974,7 +983,7 @@ __global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTVie
     // the staged operands, then the reflectors; the carry of at most kb rows in the next core
     if (left_stage_elems<T>(sd) * sizeof(T) > (size_t)zleft_lds<T>() ||
         sizeof(double2) * (size_t)kb * ZL_ROWS > (size_t)zleft_lds<T>() ||
-        sizeof(double2) * (int64_t)kb * p > (int64_t)sizeof(T) * core_capacity(l + 1, n, cap))
+        sizeof(double2) * (int64_t)kb * p > (int64_t)sizeof(T) * core_capacity(l + 1, n, ycap))
       break;
     const T *Wl = Wc + w.coff(n, l), *Al = Xc + x.coff(b, l);
     T *Yout = Yc + y.coff(b, l);
@@ -1131,13 +1140,13 @@ static cm_status zip_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, doub
   if (x->dtype == CM_C64) {
     if (left)
       hipLaunchKernelGGL(k_zip_left<float2>, dim3(batch), dim3(64), zleft_lds<float2>(), s, vw, w_by_n->batch, vx, vy,
-                         tol, cap_rank);
+                         tol, cap_rank, y->cap_rank);
     hipLaunchKernelGGL(k_zipup<float2>, dim3(slots), dim3(CM_WG), zlds_bytes<float2>(), s, vw, w_by_n->batch, vx, vy,
                        tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
   } else {
     if (left)
       hipLaunchKernelGGL(k_zip_left<double2>, dim3(batch), dim3(64), zleft_lds<double2>(), s, vw, w_by_n->batch, vx,
-                         vy, tol, cap_rank);
+                         vy, tol, cap_rank, y->cap_rank);
     hipLaunchKernelGGL(k_zipup<double2>, dim3(slots), dim3(CM_WG), zlds_bytes<double2>(), s, vw, w_by_n->batch, vx,
                        vy, tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
   }

@@ -30,3 +30,88 @@ def test_sampler_train_of_no_cores(cap):
     for b in (0, 2):
         np.testing.assert_array_equal(out[b], got[3][0][b])
         assert norm2[b] == got[3][1][b]
+
+
+# ------------------------------------------------------------------ zip-up: large batches
+
+LARGE = 1792   # a batch whose left sites run one wave per instance
+
+
+def _zip_case(model, n, dtype, batch, seed=3, cap=32, tol=1e-8):
+    import cm_workloads as W
+    make = {"heston": lambda: W.heston_batch(8, seed=seed, n=n), "bs": lambda: W.bs_batch(8, n=n),
+            "vg": lambda: W.vg_batch(8, n=n)}[model]
+    probs = make()
+    pr = cm.SfftPricer([probs[i % 8] for i in range(batch)], dtype, tol=tol, cap=cap)
+    pr.build()
+    return pr
+
+
+def _first8(pr):
+    """A pricer of the first eight instances with pr's own input trains."""
+    few = cm.SfftPricer([pr.problems[i] for i in range(8)], pr.dtype, tol=pr.tol, cap=pr.cap, mpo=pr.mpo)
+    few.x.cores.copy_(pr.x.cores[:len(few.x.cores)])
+    few.x.ranks.copy_(pr.x.ranks[:8])
+    few.x.struct.flags = pr.x.struct.flags
+    return few
+
+
+def _table(like, core_off, cores):
+    """A TTBatch of like's trains with a table of offsets and cores of its own."""
+    t = cm.TTBatch(like.ns, 2, 1, like.cap_rank, like.dtype)
+    t.core_off, t.cores = core_off, cores
+    s = t._s
+    t._s = cm.CmTTBatch(s.batch, 2, 1, s.cap_rank, s.n_max, s.dtype, 0, 0, t.n.data_ptr(), t.ranks.data_ptr(),
+                        core_off.data_ptr(), cores.data_ptr())
+    return t
+
+
+@pytest.mark.parametrize("dtype", [cm.CM_C64, cm.CM_C128])
+@pytest.mark.parametrize("n", [3, 14, 24])
+def test_zip_keeps_to_tight_tables(dtype, n):
+    """Output cores packed to the ranks they end with, thirty elements between neighbours: the apply
+    writes the cores that a small batch writes into the capacity layout (the same kernel takes both),
+    and nothing else."""
+    pr = _zip_case("heston", n, dtype, LARGE)
+    few = _first8(pr)
+    few.apply()
+    ranks = few.y.ranks.long()
+    gap, reps = 30, LARGE // 8
+    size = (ranks[:, :n] * 2 * ranks[:, 1:n + 1] + gap).repeat(reps, 1)
+    start = (torch.cumsum(size.reshape(-1), 0) - size.reshape(-1) + gap).reshape(LARGE, n)
+    off = torch.zeros((LARGE, cm.CM_MAX_N), dtype=torch.int64, device="cuda")
+    off[:, :n] = start
+    cores = torch.full((int(size.sum()) + 4096,), 1234.5, dtype=few.y.cores.dtype, device="cuda")
+    pr.y = _table(pr.y, off, cores)
+    pr.apply()
+    assert int(pr.st_apply.abs().sum()) == 0
+    assert torch.equal(pr.y.ranks[:, :n + 1], few.y.ranks[:, :n + 1].repeat(reps, 1))
+    count = (size - gap).reshape(-1)
+    within = torch.arange(int(count.sum()), device="cuda") - torch.repeat_interleave(torch.cumsum(count, 0) - count, count)
+    at = torch.repeat_interleave(start.reshape(-1), count) + within
+    ref = few.y.cores[torch.repeat_interleave(few.y.core_off[:, :n].repeat(reps, 1).reshape(-1), count) + within]
+    assert torch.equal(torch.view_as_real(cores[at]), torch.view_as_real(ref))
+    rest = torch.ones(len(cores), dtype=torch.bool, device="cuda")
+    rest[at] = False
+    assert bool((cores[rest] == 1234.5).all())
+
+
+@pytest.mark.parametrize("model,n", [("heston", 14), ("heston", 24), ("vg", 18), ("bs", 20)])
+def test_zip_left_part_fp64(model, n):
+    """Complex128 trains of a large batch, whose left sites run one wave per instance, against a small
+    batch's: the same ranks, and at tolerance 1e-10 prices in the window 0.5 <= K/S0 <= 1.5 that lie
+    within a few times 1e-10 S0 of the grid's own on either side, so within 1e-9 S0 of each other."""
+    import cm_workloads as W
+    many = _zip_case(model, n, cm.CM_C128, LARGE, tol=1e-10)
+    few = _first8(many)
+    few.apply()
+    many.apply()
+    assert int(many.st_apply.abs().sum()) == 0
+    assert torch.equal(many.y.ranks[:, :n + 1], few.y.ranks[:, :n + 1].repeat(LARGE // 8, 1))
+    u = [W.window_strided(p, 64) for p in few.problems]
+    nk = min(len(v) for v in u)
+    s = torch.from_numpy(np.stack([v[:nk] for v in u])).cuda()
+    a = few.run(s).cpu().numpy()
+    b = many.run(s.repeat(LARGE // 8, 1)).cpu().numpy()
+    assert np.array_equal(b[:8], b[-8:])
+    assert np.abs(a - b[:8]).max() <= 1e-9 * few.problems[0].S0
