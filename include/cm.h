@@ -177,8 +177,8 @@ cm_status cm_build_qtt(const cm_problem *prob, int batch, double tol, int cap_ra
  * y: trains with y->n[b] == x->n[b], d_out = 2, d_in = 1; on return y->flags =
  * CM_TT_LEFT_ORTHO. A train whose offsets are spaced as cm_tt_layout spaces them for
  * y->cap_rank may have the room beyond its cores' ranks overwritten (large batches keep
- * carries there); in any other table nothing but the cores themselves is written.
- * status: device [batch].
+ * carries there); in any other table nothing but the cores themselves is written. y's cores
+ * may be x's buffer under the same offsets. status: device [batch].
  * Workspace: cm_workspace_bytes(CM_OP_SFFT_APPLY, batch, x->n_max, cap_rank, dtype). */
 cm_status cm_sfft_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, double tol, int cap_rank,
                         cm_tt_batch *y, int32_t *status, void *ws, size_t ws_bytes, void *stream);

@@ -1135,8 +1135,8 @@ static cm_status zip_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, doub
   TTView vw = tt_view(w_by_n), vx = tt_view(x), vy = tt_view(y);
   CM_HIP_CHECK(cm_allow_lds(k_zipup<float2>, zlds_bytes<float2>()));
   CM_HIP_CHECK(cm_allow_lds(k_zipup<double2>, zlds_bytes<double2>()));
-  // the left part needs next cores that hold its carries
-  const int left = cap_rank >= ZLEFT_CAP && batch >= ZLEFT_BATCH;
+  // the left part needs next cores that hold its carries, and x's cores to stay as they are
+  const int left = cap_rank >= ZLEFT_CAP && batch >= ZLEFT_BATCH && x->cores != y->cores;
   if (x->dtype == CM_C64) {
     if (left)
       hipLaunchKernelGGL(k_zip_left<float2>, dim3(batch), dim3(64), zleft_lds<float2>(), s, vw, w_by_n->batch, vx, vy,

@@ -96,6 +96,26 @@ def test_zip_keeps_to_tight_tables(dtype, n):
     assert bool((cores[rest] == 1234.5).all())
 
 
+@pytest.mark.parametrize("dtype", [cm.CM_C64, cm.CM_C128])
+@pytest.mark.parametrize("n", [14, 24])
+def test_zip_into_its_input(dtype, n):
+    """The output cores may be the input's buffer under the same offsets, in any batch: the cores are
+    those of a small batch, bit for bit (the same kernel takes both)."""
+    pr = _zip_case("heston", n, dtype, LARGE)
+    ref = _first8(pr)
+    ref.apply()
+    pr.y = _table(pr.y, pr.x.core_off, pr.x.cores)
+    pr.apply()
+    assert int(pr.st_apply.abs().sum()) == 0
+    assert torch.equal(pr.y.ranks[:, :n + 1], ref.y.ranks[:, :n + 1].repeat(LARGE // 8, 1))
+    rk = ref.y.ranks.cpu().numpy()
+    for b in (0, 3, 7, LARGE - 2):
+        for l in range(n):
+            k = int(rk[b % 8, l] * 2 * rk[b % 8, l + 1])
+            o, p = int(pr.y.core_off[b, l]), int(ref.y.core_off[b % 8, l])
+            assert torch.equal(torch.view_as_real(pr.y.cores[o:o + k]), torch.view_as_real(ref.y.cores[p:p + k])), (b, l)
+
+
 @pytest.mark.parametrize("model,n", [("heston", 14), ("heston", 24), ("vg", 18), ("bs", 20)])
 def test_zip_left_part_fp64(model, n):
     """Complex128 trains of a large batch, whose left sites run one wave per instance, against a small
