@@ -661,11 +661,14 @@ __device__ __forceinline__ int zip_site_pair(char *arena, const SiteDims &sd, co
 // stops at the first site that is too large (or whose carry would not fit), leaves the site
 // and the status in y's last rank entry, and k_zipup goes on from there.
 constexpr int ZL_ROWS = 32, ZL_COLS = 32;   // largest site
-// Smallest capacity of y, whose cores hold the carries, and smallest batch for which the left part
-// runs apart. Alone on a CU its sites take longer than on four waves (one wave does all of a
-// site's work: 512 trains of n = 24 1.27 against 1.15 ms, 768 1.44 against 1.36); from four
-// trains a CU on it wins (1024 2.03 against 2.12 ms, 2048 2.99 against 3.31, 4096 5.80 against 6.48).
-constexpr int ZLEFT_CAP = 16, ZLEFT_BATCH = 1024;
+// Smallest capacity of y, whose cores hold the carries, smallest batch and smallest n_max for which
+// the left part runs apart. One wave does all of a site's work, so it pays only once the CU's eight
+// places are nearly full: from seven trains a CU on (1792) it took 0.72 to 1.00 of the time without
+// it over Heston, Black-Scholes, Merton and Variance Gamma chains of n = 14..28 at tolerances 1e-5
+// to 1e-10 in both types (n = 24 Heston, 4096 trains: 5.80 against 6.48 ms), while at 1024 and 1500
+// trains it took up to 1.05 times as long from n = 14 on. Chains of n <= 12 at 1e-8, whose bonds reach
+// the largest small sites at once, lose at larger batches too (Variance Gamma, n = 12, 2048: 1.11).
+constexpr int ZLEFT_CAP = 16, ZLEFT_BATCH = 1792, ZLEFT_N = 14;
 template <typename T> constexpr int zleft_lds() { return sizeof(T) == 8 ? 12 * 1024 : 20 * 1024; }
 // y.ranks[n] between the two kernels: -(site + 1) - 64 status (0: start from the first site)
 __device__ __forceinline__ int zleft_mark(int site, int code) { return -(site + 1) - 64 * code; }
@@ -1003,10 +1006,11 @@ __global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTVie
   }
 }
 
-template <typename T>
+// LEFT: k_zip_left has run before (a switch at run time spills 56 registers instead of 51 for every batch).
+template <typename T, bool LEFT>
 __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTView x, TTView y, double tol, int cap,
                                                  int batch, int32_t *__restrict__ status,
-                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap, int left) {
+                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap) {
   extern __shared__ __align__(16) char lds_arena[];
   __shared__ la::Sh sh;
   __shared__ int code_sh;
@@ -1049,7 +1053,7 @@ __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTVie
     }
     const double delta2 = (n > 1) ? tol * tol * xn2_sh / (double)(n - 1) : 0.0;
     // where k_zip_left stopped: its carry moves from y's core l0 to the slab
-    const int mark = left ? -y.rk(b)[n] : 0;
+    const int mark = LEFT ? -y.rk(b)[n] : 0;
     const int l0 = mark > 0 ? (mark - 1) & 63 : 0;
     int chi = l0 > 0 ? y.rk(b)[l0] : 1;
     if (l0 > 0) {
@@ -1062,7 +1066,7 @@ __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTVie
       y.rk(b)[0] = 1;
     }
     __syncthreads();
-    if (left && tid == 0) y.rk(b)[n] = 1;   // a rank again, also for a chain that ends early
+    if (LEFT && tid == 0) y.rk(b)[n] = 1;   // a rank again, also for a chain that ends early
     for (int l = l0; l < n; ++l) {
       SiteDims sd;
       sd.chi = chi; sd.w0 = wr[l]; sd.w1 = wr[l + 1]; sd.r0 = xr[l]; sd.r1 = xr[l + 1];
@@ -1133,23 +1137,23 @@ static cm_status zip_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, doub
   const int64_t mc = (int64_t)zip_mat_cap(cap_rank);
   hipStream_t s = (hipStream_t)stream;
   TTView vw = tt_view(w_by_n), vx = tt_view(x), vy = tt_view(y);
-  CM_HIP_CHECK(cm_allow_lds(k_zipup<float2>, zlds_bytes<float2>()));
-  CM_HIP_CHECK(cm_allow_lds(k_zipup<double2>, zlds_bytes<double2>()));
   // the left part needs next cores that hold its carries, and x's cores to stay as they are
-  const int left = cap_rank >= ZLEFT_CAP && batch >= ZLEFT_BATCH && x->cores != y->cores;
-  if (x->dtype == CM_C64) {
-    if (left)
-      hipLaunchKernelGGL(k_zip_left<float2>, dim3(batch), dim3(64), zleft_lds<float2>(), s, vw, w_by_n->batch, vx, vy,
-                         tol, cap_rank, y->cap_rank);
-    hipLaunchKernelGGL(k_zipup<float2>, dim3(slots), dim3(CM_WG), zlds_bytes<float2>(), s, vw, w_by_n->batch, vx, vy,
-                       tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
-  } else {
-    if (left)
-      hipLaunchKernelGGL(k_zip_left<double2>, dim3(batch), dim3(64), zleft_lds<double2>(), s, vw, w_by_n->batch, vx,
-                         vy, tol, cap_rank, y->cap_rank);
-    hipLaunchKernelGGL(k_zipup<double2>, dim3(slots), dim3(CM_WG), zlds_bytes<double2>(), s, vw, w_by_n->batch, vx,
-                       vy, tol, cap_rank, batch, status, (char *)ws, slab, mc, left);
-  }
+  const bool left =
+      cap_rank >= ZLEFT_CAP && batch >= ZLEFT_BATCH && x->n_max >= ZLEFT_N && x->cores != y->cores;
+  auto launch = [&](auto zero, auto with_left) -> cm_status {
+    using T = decltype(zero);
+    constexpr bool LEFT = decltype(with_left)::value;
+    CM_HIP_CHECK(cm_allow_lds(k_zipup<T, LEFT>, zlds_bytes<T>()));
+    if (LEFT)
+      hipLaunchKernelGGL(k_zip_left<T>, dim3(batch), dim3(64), zleft_lds<T>(), s, vw, w_by_n->batch, vx, vy, tol,
+                         cap_rank, y->cap_rank);
+    hipLaunchKernelGGL((k_zipup<T, LEFT>), dim3(slots), dim3(CM_WG), zlds_bytes<T>(), s, vw, w_by_n->batch, vx, vy, tol,
+                       cap_rank, batch, status, (char *)ws, slab, mc);
+    return CM_OK;
+  };
+  const cm_status e = x->dtype == CM_C64 ? (left ? launch(float2{}, std::true_type{}) : launch(float2{}, std::false_type{}))
+                                         : (left ? launch(double2{}, std::true_type{}) : launch(double2{}, std::false_type{}));
+  if (e != CM_OK) return e;
   CM_LAUNCH_CHECK();
   y->flags = CM_TT_LEFT_ORTHO;
   return CM_OK;

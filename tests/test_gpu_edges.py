@@ -34,7 +34,7 @@ def test_sampler_train_of_no_cores(cap):
 
 # ------------------------------------------------------------------ zip-up: large batches
 
-LARGE = 1792   # a batch whose left sites run one wave per instance
+LARGE = 1792   # the smallest batch whose left sites run one wave per instance (from n = 14 on)
 
 
 def _zip_case(model, n, dtype, batch, seed=3, cap=32, tol=1e-8):
@@ -135,3 +135,22 @@ def test_zip_left_part_fp64(model, n):
     b = many.run(s.repeat(LARGE // 8, 1)).cpu().numpy()
     assert np.array_equal(b[:8], b[-8:])
     assert np.abs(a - b[:8]).max() <= 1e-9 * few.problems[0].S0
+
+
+@pytest.mark.parametrize("n", [13, 14])
+@pytest.mark.parametrize("batch", [LARGE - 1, LARGE])
+def test_zip_left_rule(batch, n):
+    """Either side of the rule for the left part, complex64: the ranks, statuses and prices of a small
+    batch with the same inputs (the cores may differ by the last bit of FP64 sums before they are
+    rounded; prices by 1e-6 S0 at most, the accuracy of a complex64 chain at tolerance 1e-8)."""
+    import cm_workloads as W
+    many = _zip_case("heston", n, cm.CM_C64, batch)
+    few = _first8(many)
+    few.apply()
+    many.apply()
+    k = torch.arange(batch, device="cuda") % 8
+    assert int(many.st_apply.abs().sum()) == 0
+    assert torch.equal(many.y.ranks[:, :n + 1], few.y.ranks[k, :n + 1])
+    s = torch.from_numpy(np.stack([W.near_money(p, 64) for p in few.problems])).cuda()
+    a, b = few.run(s), many.run(s[k])
+    assert float((a[k] - b).abs().max()) <= 1e-6 * few.problems[0].S0
