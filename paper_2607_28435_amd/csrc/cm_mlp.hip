@@ -37,8 +37,41 @@ __host__ __device__ constexpr int wfrag(int n, int k) {
   return ((((n >> 5) * 16 + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (n & 31)) << 3) + (k & 7);
 }
 
-// SiLU from the hardware exp2 and reciprocal (a few ulps): for the activation operand of the
-// layer GEMMs, whose hi + lo BF16 split keeps about 2^-16 of it anyway. Large |z| behave:
+// sigmoid(z) = 1 / (1 + e^-z) and silu(z) = z sigmoid(z), as exact as expf and an IEEE division give
+// them in half the instructions: e^-|z| from the hardware exp2 with the argument's rounding put back
+// (log2 e as two FP32 numbers), the quotient by the hardware reciprocal and one correction, which
+// for silu also takes the roundings of 1 + e^-|z| and z e^-|z|.
+struct Sig {
+  float u, d, r;   // e^-|z|, 1 + u, about 1 / d
+  bool neg;
+  __device__ __forceinline__ explicit Sig(float z) {
+    const float a = fminf(fabsf(z), 200.0f);   // beyond, e^-a is 0
+    const float t = -1.44269502f * a;
+    const float lo = fmaf(-1.92596299e-8f, a, fmaf(-1.44269502f, a, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    u = fmaf(e, 0.693147181f * lo, e);
+    d = 1.0f + u;
+    r = __builtin_amdgcn_rcpf(d);
+    neg = z < 0.0f;
+  }
+  __device__ __forceinline__ float sigmoid() const {
+    const float n = neg ? u : 1.0f, q = n * r;
+    return fmaf(r, fmaf(-d, q, n), q);
+  }
+  __device__ __forceinline__ float silu(float z) const {
+    const float m = neg ? u : 1.0f, n = z * m, q = n * r;
+    return fmaf(r, fmaf(-d, q, n) + fmaf((d - 1.0f) - u, q, fmaf(z, m, -n)), q);
+  }
+  __device__ __forceinline__ float silu_grad(float z) const {
+    const float s = sigmoid();
+    return s * (1.0f + z * (1.0f - s));
+  }
+};
+__device__ __forceinline__ float silu_f(float z) { return Sig(z).silu(z); }
+// SiLU from the hardware exp2 and reciprocal: for the activation operands of the layer products, of
+// which one BF16 part or two keep 2^-8 or 2^-16, and for inference. Its relative error grows with |z|
+// (the exponent's argument is rounded: 40 units of 2^-24 at z = -80), so what training keeps in
+// FP32 (predictions, deltas, the gradients of W5) takes silu_f. Large |z| behave:
 // exp2 overflows to inf and the reciprocal to 0 (z -> -inf), or exp2 goes to 0 (z -> +inf).
 __device__ __forceinline__ float silu_fast(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
@@ -417,7 +450,8 @@ __global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, i
         *(float4 *)&Z[((int64_t)(l - 2) * B + q) * NW + n] =
             make_float4(acc[0][4 * g], acc[0][4 * g + 1], acc[0][4 * g + 2], acc[0][4 * g + 3]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[4 * g + j] = silu_fast(acc[0][4 * g + j]);
+      for (int j = 0; j < 4; ++j)
+        v[4 * g + j] = KEEP && l == 5 ? silu_f(acc[0][4 * g + j]) : silu_fast(acc[0][4 * g + j]);
     }
     if (l == 5) {
       float s = 0.0f;
@@ -504,15 +538,6 @@ __global__ __launch_bounds__(256) void k_bwd_mid(float *__restrict__ grad) {
   }
 }
 
-// sigmoid from the hardware exp2 and reciprocal (see silu_fast)
-__device__ __forceinline__ float sig_fast(float z) {
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
-}
-__device__ __forceinline__ float silu_grad_fast(float z) {
-  const float s = sig_fast(z);
-  return s * (1.0f + z * (1.0f - s));
-}
-
 // delta_4 = dy W5 silu'(Z4), delta_{l-1} = (delta_l W_l) silu'(Z_{l-1}) for a tile of 32 rows;
 // delta_3 and delta_2 go to D ([2][B][256]), delta_1 stays on chip and is summed into W1's and
 // b1's gradients (FP32, one atomic per gradient and tile, to one of their copies).
@@ -540,10 +565,10 @@ __global__ __launch_bounds__(TWG) void k_mlp_bwd(const float *__restrict__ x, co
     for (int g = 0; g < 4; ++g) {
       const int n = 32 * w + 8 * g + 4 * hi32;
       const float4 z = *(const float4 *)&Z[3 * BN + zrow + n];
-      v[4 * g] = d * p[OFF_W5 + n] * silu_grad_fast(z.x);
-      v[4 * g + 1] = d * p[OFF_W5 + n + 1] * silu_grad_fast(z.y);
-      v[4 * g + 2] = d * p[OFF_W5 + n + 2] * silu_grad_fast(z.z);
-      v[4 * g + 3] = d * p[OFF_W5 + n + 3] * silu_grad_fast(z.w);
+      v[4 * g] = d * p[OFF_W5 + n] * Sig(z.x).silu_grad(z.x);
+      v[4 * g + 1] = d * p[OFF_W5 + n + 1] * Sig(z.y).silu_grad(z.y);
+      v[4 * g + 2] = d * p[OFF_W5 + n + 2] * Sig(z.z).silu_grad(z.z);
+      v[4 * g + 3] = d * p[OFF_W5 + n + 3] * Sig(z.w).silu_grad(z.w);
       put4(tl, l32, n, v + 4 * g);
     }
   }
@@ -561,10 +586,10 @@ __global__ __launch_bounds__(TWG) void k_mlp_bwd(const float *__restrict__ x, co
     if (l > 2) load_frags(wt + (int64_t)(l - 3) * NW * NW, w, lane, f);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      v[4 * g] = (acc[0][4 * g] + acc[1][4 * g]) * silu_grad_fast(z[g].x);
-      v[4 * g + 1] = (acc[0][4 * g + 1] + acc[1][4 * g + 1]) * silu_grad_fast(z[g].y);
-      v[4 * g + 2] = (acc[0][4 * g + 2] + acc[1][4 * g + 2]) * silu_grad_fast(z[g].z);
-      v[4 * g + 3] = (acc[0][4 * g + 3] + acc[1][4 * g + 3]) * silu_grad_fast(z[g].w);
+      v[4 * g] = (acc[0][4 * g] + acc[1][4 * g]) * Sig(z[g].x).silu_grad(z[g].x);
+      v[4 * g + 1] = (acc[0][4 * g + 1] + acc[1][4 * g + 1]) * Sig(z[g].y).silu_grad(z[g].y);
+      v[4 * g + 2] = (acc[0][4 * g + 2] + acc[1][4 * g + 2]) * Sig(z[g].z).silu_grad(z[g].z);
+      v[4 * g + 3] = (acc[0][4 * g + 3] + acc[1][4 * g + 3]) * Sig(z[g].w).silu_grad(z[g].w);
       const int n = 32 * w + 8 * g + 4 * hi32;
       if (l > 2) {
         put4(tl + ((l - 1) & 1) * TILE_BUF, l32, n, v + 4 * g);
@@ -690,13 +715,14 @@ __global__ __launch_bounds__(256) void k_wgrad(const float *__restrict__ Z, cons
         // rows past the span carry zeros in a and d
         a[i] = cur.a[h][i];
         if (layer == 4) {
-          const float z = a[i], sg = sig_fast(z);
-          a[i] = cur.d[h][i] * w5 * (sg * (1.0f + z * (1.0f - sg)));
-          g5 += cur.d[h][i] * (z * sg);
+          const float z = a[i];
+          const Sig sg(z);
+          a[i] = cur.d[h][i] * w5 * sg.silu_grad(z);
+          g5 += cur.d[h][i] * sg.silu(z);
           gd += cur.d[h][i];
         }
         gb += a[i];
-        s[i] = silu_fast(cur.b[h][i]);
+        s[i] = silu_fast(cur.b[h][i]);   // rounded to BF16 next
       }
       s16x8 hi, lo, sb;
       split8(a, hi, lo);

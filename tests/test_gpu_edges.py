@@ -154,3 +154,40 @@ def test_zip_left_rule(batch, n):
     s = torch.from_numpy(np.stack([W.near_money(p, 64) for p in few.problems])).cuda()
     a, b = few.run(s), many.run(s[k])
     assert float((a[k] - b).abs().max()) <= 1e-6 * few.problems[0].S0
+
+
+# ------------------------------------------------------------------ surrogate
+
+@pytest.mark.parametrize("B", [1, 33, 300])
+def test_training_keeps_the_accurate_silu(B):
+    """Fourth-layer neurons far on the flat side (z near -80), one of them read by the output: the
+    prediction is W5 silu(z) alone, and the gradients of W5 and b4 sums of silu(z) and silu'(z). From
+    the pre-activations the call has kept, FP64 gives them; the call's roundings are the exponential's
+    (2 units of 2^-24 relative), the sum's, the quotient's and the products' (one each), 8 in all, and
+    one per term for the sum over the batch. An exponential whose argument is rounded would be off by
+    up to 80 of them."""
+    from test_gpu_launch_shapes import _mlp_case
+    net, x, _ = _mlp_case(B, 21)
+    p = net.params
+    p[199168:199424] = -80.0
+    p[199424:199680] = 0.0
+    p[199424 + 5] = 1.0
+    p[199680] = 0.0
+    cm.cm_mlp_sync_bf16(net.struct)
+    nb = cm.cm_mlp_act_bytes(B)
+    acts = torch.empty(nb // 4, dtype=torch.float32, device="cuda")
+    ws = torch.empty(nb // 2, dtype=torch.uint8, device="cuda")
+    y = torch.empty(B, dtype=torch.float32, device="cuda")
+    grad = torch.empty(cm.CM_MLP_NPARAMS, dtype=torch.float32, device="cuda")
+    dy = torch.ones(B, dtype=torch.float32, device="cuda")
+    cm.cm_mlp_forward(net.struct, x, B, y, acts, nb)
+    cm.cm_mlp_backward(net.struct, x, acts, dy, B, grad, ws, nb // 2)
+    z = acts[3 * B * 256:].reshape(B, 256).double()
+    assert float(z.max()) < -60.0 and float(z.min()) > -87.0
+    s = torch.sigmoid(z)
+    silu, slope = z * s, s * (1.0 + z * (1.0 - s))
+    eps = 2.0 ** -24
+    rel = lambda a, b: float(((a.double() - b) / b).abs().max()) / eps
+    assert rel(y, silu[:, 5]) <= 8
+    assert rel(grad[199424:199680], silu.sum(0)) <= 8 + B
+    assert rel(grad[199168 + 5:199168 + 6], slope[:, 5].sum(0, keepdim=True)) <= 8 + B
