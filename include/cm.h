@@ -318,8 +318,8 @@ cm_status cm_mlp_sync_bf16(const cm_mlp *net, void *stream);
  * acts: device buffer of acts_bytes bytes. With acts_bytes >= cm_mlp_act_bytes(B) the
  * pre-activations Z1..Z4 are kept there for cm_mlp_backward (16-byte aligned). Otherwise
  * (inference; acts may be NULL) nothing is kept. Either way one launch runs all five layers with
- * the activations on chip; outputs of different batch sizes agree to FP32 rounding (the kernel
- * for large batches adds in another order). */
+ * the activations on chip. A query's output without acts does not depend on its batch; with acts
+ * it agrees to FP32 rounding (the sums run in another order). */
 cm_status cm_mlp_forward(const cm_mlp *net, const float *x, int B, float *y, float *acts, size_t acts_bytes,
                          void *stream);
 

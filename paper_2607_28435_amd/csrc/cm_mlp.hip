@@ -389,20 +389,58 @@ __device__ __forceinline__ void tile_product(const uint16_t *buf, int lane, cons
   }
 }
 
-// y[b] = network(x[b]); with KEEP the pre-activations Z1..Z4 go to Z ([4][B][256]).
+// The same with one chain, hi before lo in every K step, as k_mlp_fused adds.
+__device__ __forceinline__ void tile_product_1(const uint16_t *buf, int lane, const s16x8 *f, f32x16 &acc) {
+  const uint16_t *src = buf + (lane & 31) * FP + 8 * (lane >> 5);
+#pragma unroll
+  for (int ks = 0; ks < TKS; ++ks) {
+    const bf16x8 A = __builtin_bit_cast(bf16x8, f[ks]);
+    const s16x8 bh = *(const s16x8 *)(src + 16 * ks), bl = *(const s16x8 *)(src + TM * FP + 16 * ks);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, bh), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, bl), acc, 0, 0, 0);
+  }
+}
+
+// y[b] = network(x[b]). With KEEP (training) the pre-activations Z1..Z4 go to Z ([4][B][256]), layer 1
+// is summed in FP32 and the two operand parts in chains of their own. Without it (inference) every
+// sum is formed by k_mlp_fused's operations in its order, so that a row's output does not depend
+// on the batch it came in: with sums of its own this kernel was off by 6.6e-8 of the outputs'
+// norm where k_mlp_fused is by 4.7e-8 (777 to 24000 rows, against FP64).
 template <bool KEEP>
 __global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, int B, const float *__restrict__ p,
                                                   const uint16_t *__restrict__ wbf, cm_mlp net,
                                                   float *__restrict__ y, float *__restrict__ Z) {
   extern __shared__ __align__(16) uint16_t tl[];
-  __shared__ __align__(16) float w1s[NW * NIN], bsh[4][NW], w5s[NW];
-  __shared__ float xs[TM][NIN + 1], ys[8][TM];
+  __shared__ __align__(16) float w1s[KEEP ? NW * NIN : 4], bsh[4][NW], w5s[NW];
+  __shared__ float xs[KEEP ? TM : 1][NIN + 1], ys[8][TM], half[4][64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int l32 = lane & 31, hi32 = lane >> 5;
   const int q0 = blockIdx.x * TM, q = q0 + l32;
   s16x8 f[TKS];
   load_frags(wbf, w, lane, f);
-  for (int e = tid; e < NW * NIN; e += TWG) w1s[e] = p[OFF_W1 + e];
+  bf16x8 w1h, w1l, xh, xl;   // layer 1's operands (inference)
+  if constexpr (KEEP) {
+    for (int e = tid; e < NW * NIN; e += TWG) w1s[e] = p[OFF_W1 + e];
+    if (tid < TM * NIN) {
+      const int r = tid / NIN, i = tid % NIN;
+      xs[r][i] = q0 + r < B ? (x[(int64_t)(q0 + r) * NIN + i] - net.shift[i]) * net.scale[i] : 0.0f;
+    }
+  } else {
+    float a[8], b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int k = 8 * hi32 + i;
+      a[i] = k < NIN ? p[OFF_W1 + (32 * w + l32) * NIN + k] : 0.0f;
+      b[i] = (k < NIN && q < B) ? (x[(int64_t)q * NIN + k] - net.shift[k]) * net.scale[k] : 0.0f;
+    }
+    s16x8 h, l;
+    split8(a, h, l);
+    w1h = __builtin_bit_cast(bf16x8, h);
+    w1l = __builtin_bit_cast(bf16x8, l);
+    split8(b, h, l);
+    xh = __builtin_bit_cast(bf16x8, h);
+    xl = __builtin_bit_cast(bf16x8, l);
+  }
   for (int e = tid; e < NW; e += TWG) {
     bsh[0][e] = p[OFF_B1 + e];
     bsh[1][e] = p[off_b(2) + e];
@@ -410,14 +448,17 @@ __global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, i
     bsh[3][e] = p[off_b(4) + e];
     w5s[e] = p[OFF_W5 + e];
   }
-  if (tid < TM * NIN) {
-    const int r = tid / NIN, i = tid % NIN;
-    xs[r][i] = q0 + r < B ? (x[(int64_t)(q0 + r) * NIN + i] - net.shift[i]) * net.scale[i] : 0.0f;
-  }
   __syncthreads();
   f32x16 acc[2];
   // accumulator v of this lane: neuron 32 w + 8 (v / 4) + 4 hi32 + v mod 4 of row l32
-  {
+  auto bias_init = [&](const float *bias) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b4 = *(const float4 *)&bias[32 * w + 8 * g + 4 * hi32];
+      acc[0][4 * g] = b4.x; acc[0][4 * g + 1] = b4.y; acc[0][4 * g + 2] = b4.z; acc[0][4 * g + 3] = b4.w;
+    }
+  };
+  if constexpr (KEEP) {
     float xr[NIN];
 #pragma unroll
     for (int i = 0; i < NIN; ++i) xr[i] = xs[l32][i];
@@ -438,6 +479,11 @@ __global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, i
         acc[0][4 * g + j] = s;
       }
     }
+  } else {
+    bias_init(bsh[0]);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1h, xh, acc[0], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1h, xl, acc[0], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1l, xh, acc[0], 0, 0, 0);
   }
 #pragma unroll
   for (int l = 2; l <= 5; ++l) {
@@ -455,34 +501,48 @@ __global__ __launch_bounds__(TWG) void k_mlp_tile(const float *__restrict__ x, i
     }
     if (l == 5) {
       float s = 0.0f;
+      auto fold = [&]() {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) s += w5s[32 * w + 8 * (k >> 2) + 4 * hi32 + (k & 3)] * v[k];
+        for (int k = 0; k < 16; ++k) s += w5s[32 * w + 8 * (k >> 2) + 4 * hi32 + (k & 3)] * v[k];
+      };
+      if (KEEP || !(w & 1)) fold();
+      if constexpr (!KEEP) {   // a lane of k_mlp_fused adds the neurons of two waves here, the even one's first
+        if (!(w & 1)) half[w >> 1][lane] = s;
+        __syncthreads();
+        if (w & 1) {
+          s = half[w >> 1][lane];
+          fold();
+        }
+      }
       s += __shfl_xor(s, 32, 64);
       if (hi32 == 0) ys[w][l32] = s;
     } else {
       uint16_t *buf = tl + (l & 1) * TILE_BUF;
 #pragma unroll
       for (int g = 0; g < 4; ++g) put4(buf, l32, 32 * w + 8 * g + 4 * hi32, v + 4 * g);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 b4 = *(const float4 *)&bsh[l - 1][32 * w + 8 * g + 4 * hi32];
-        acc[0][4 * g] = b4.x; acc[0][4 * g + 1] = b4.y; acc[0][4 * g + 2] = b4.z; acc[0][4 * g + 3] = b4.w;
-      }
+      bias_init(bsh[l - 1]);
 #pragma unroll
       for (int k = 0; k < 16; ++k) acc[1][k] = 0.0f;
       __syncthreads();
-      tile_product(buf, lane, f, acc);
+      if constexpr (KEEP) tile_product(buf, lane, f, acc);
+      else tile_product_1(buf, lane, f, acc[0]);
       if (l < 4) load_frags(wbf + (int64_t)(l - 1) * NW * NW, w, lane, f);
+      if constexpr (KEEP) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) acc[0][k] += acc[1][k];
+        for (int k = 0; k < 16; ++k) acc[0][k] += acc[1][k];
+      }
     }
   }
   __syncthreads();
   if (tid < TM && q0 + tid < B) {
-    float s = p[OFF_B5];
+    if constexpr (KEEP) {
+      float s = p[OFF_B5];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += ys[k][tid];
-    y[q0 + tid] = s;
+      for (int k = 0; k < 8; ++k) s += ys[k][tid];
+      y[q0 + tid] = s;
+    } else {
+      y[q0 + tid] = ((ys[1][tid] + ys[3][tid]) + (ys[5][tid] + ys[7][tid])) + p[OFF_B5];
+    }
   }
 }
 

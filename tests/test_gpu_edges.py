@@ -191,3 +191,30 @@ def test_training_keeps_the_accurate_silu(B):
     assert rel(y, silu[:, 5]) <= 8
     assert rel(grad[199424:199680], silu.sum(0)) <= 8 + B
     assert rel(grad[199168 + 5:199168 + 6], slope[:, 5].sum(0, keepdim=True)) <= 8 + B
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 33, 777, 8200, 24576])
+def test_queries_do_not_depend_on_their_batch(B):
+    """A query's output is the same bits in a small batch (tiles of 32 rows) and in a large one (two
+    tiles of 64 in flight), at the large batch's start and at its ragged end."""
+    from test_gpu_launch_shapes import _mlp_case
+    net, x, _ = _mlp_case(24577 + 70, 13)
+    every = net.forward(x)
+    assert torch.equal(net.forward(x[:B].contiguous()), every[:B])
+    assert torch.equal(net.forward(x[-B:].contiguous()), every[-B:])
+
+
+@pytest.mark.parametrize("B", [24577, 32832, 49153])
+def test_large_batches_against_the_training_forward(B):
+    """Sizes that end in a ragged tile of 64, or leave its two halves unequal numbers of tiles: the
+    inference kernel's outputs against the training forward's, whose sums run in another order. The
+    hidden operands keep 2^-16, three layers deep; 1e-4 of the largest output covers both."""
+    from test_gpu_launch_shapes import _mlp_case
+    net, x, _ = _mlp_case(B, 14)
+    nb = cm.cm_mlp_act_bytes(B)
+    acts = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    y = torch.empty(B, dtype=torch.float32, device="cuda")
+    cm.cm_mlp_forward(net.struct, x, B, y, acts, nb)
+    z = net.forward(x)
+    assert not torch.equal(y, z)
+    assert float((y - z).abs().max()) <= 1e-4 * float(z.abs().max())
