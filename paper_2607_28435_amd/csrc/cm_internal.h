@@ -110,14 +110,22 @@ __host__ __device__ __forceinline__ double frac2(double hi, double lo) {
   return f;
 }
 
-// Batches of complex128 trains up to this size take the rounding sweeps on four waves per train
-// (cm_sweep_wide.hip): two trains a CU, which the one-wave kernels leave to the latency of one
-// sweep (256 Variance Gamma trains, n = 20: build 2.27 -> 1.56 ms, rounding 1.24 -> 1.04 ms; at 1024
-// Heston trains the two measure the same to a tenth, and 4096 of n = 24 would go from 2.1 + 2.0 to
-// 5.6 + 5.4 ms). Complex64 trains stay on one wave at every size: the sums of the two run in
-// different orders, and rounding the stored cores to FP32 turns a different last bit into a
-// difference of 1e-7 in a price.
-constexpr int WIDE_BATCH = 512;
+// Batches of complex128 trains that take the rounding sweeps on four waves per train
+// (cm_sweep_wide.hip): up to one train a CU, which the one-wave kernels leave to the latency of one
+// sweep, and trains whose bonds leave four waves something to do. Bonds are not known on the host,
+// but length, tolerance and capacity bound them. One wave against four, batches of 1 to 256:
+//   n = 20..28, tolerance 1e-8: rounding 1.01 to 1.11 times as fast on four (Heston, Black-Scholes,
+//     Merton, Variance Gamma), 1e-10: 1.07 to 1.24; 1e-6: 0.89 to 0.93;
+//   n = 6..16, 1e-8: 0.88 to 1.02; n = 18: 0.99 to 1.06;
+//   the build's sweep at 1e-9 to 1e-11: 1.00 to 1.29 from n = 20 on, 0.92 to 1.06 below; 1e-7: 0.97 to 1.10.
+// Two trains a CU (300 and 512 trains): 0.80 to 1.03 at 1e-6 and 1e-8. Complex64 trains stay on one wave
+// at every size: the sums of the two run in different orders, and rounding the stored cores to FP32
+// turns a different last bit into a difference of 1e-7 in a price.
+constexpr int WIDE_BATCH = 256, WIDE_N = 20, WIDE_CAP = 16;
+constexpr double WIDE_TOL_ROUND = 1e-8, WIDE_TOL_BUILD = 1e-9;
+static inline bool wide_sweep(int batch, int n_max, int cap, double tol, double most) {
+  return batch <= WIDE_BATCH && n_max >= WIDE_N && cap >= WIDE_CAP && tol <= most;
+}
 
 // Allows a kernel to take more than the default dynamic LDS (gfx950 has 160 KB per CU).
 template <typename K>

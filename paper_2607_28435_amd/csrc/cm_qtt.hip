@@ -411,7 +411,7 @@ extern "C" cm_status cm_build_qtt(const cm_problem *prob, int batch, double tol,
     } else {
       hipLaunchKernelGGL(k_build_qtt<double2>, dim3(cnt), dim3(CM_WG), lds, s, prob, batch, base, tol, cap_rank, v,
                          status, (char *)ws, slab, x->n_max);
-      if (batch <= WIDE_BATCH) {
+      if (wide_sweep(batch, x->n_max, cap_rank, tol, WIDE_TOL_BUILD)) {
         const cm_status e = cm_build_round_wide(prob, cnt, tol, cap_rank, v, status, (char *)ws, slab, x->n_max, s);
         if (e != CM_OK) return e;
       } else {

@@ -26,7 +26,7 @@ extern "C" cm_status cm_tt_round(cm_tt_batch *t, double tol, int cap_rank, doubl
   TTView v = tt_view(t);
   hipStream_t s = (hipStream_t)stream;
   const int skip = (t->flags & CM_TT_LEFT_ORTHO) ? 1 : 0;
-  if (t->dtype == CM_C128 && t->batch <= WIDE_BATCH) {
+  if (t->dtype == CM_C128 && wide_sweep(t->batch, t->n_max, cap_rank, tol, WIDE_TOL_ROUND)) {
     const cm_status e = cm_round_wide(v, t->batch, tol, cap_rank, t->cap_rank, err_out, status, (char *)ws, slots,
                                       t->n_max, skip, s);
     if (e == CM_OK) t->flags = CM_TT_RIGHT_ORTHO;

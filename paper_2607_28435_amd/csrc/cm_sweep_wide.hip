@@ -1,5 +1,5 @@
-// The rounding sweeps on four waves per train, for batches that do not fill the chip (see
-// WIDE_BATCH).
+// The rounding sweeps on four waves per train, for small batches of long trains (see
+// wide_sweep).
 #define CM_WG 256
 #include "cm_qtt_round.h"
 #include "cm_round_kernel.h"

@@ -218,3 +218,26 @@ def test_large_batches_against_the_training_forward(B):
     z = net.forward(x)
     assert not torch.equal(y, z)
     assert float((y - z).abs().max()) <= 1e-4 * float(z.abs().max())
+
+
+# ------------------------------------------------------------------ rounding sweeps on four waves
+
+@pytest.mark.parametrize("n", [19, 20, 23])
+@pytest.mark.parametrize("tol", [2e-8, 1e-8, 1e-10])
+def test_sweeps_either_side_of_the_four_wave_rule(n, tol):
+    """Complex128 batches of 256 from n = 20 on and tolerance 1e-8 down take the sweeps on four waves
+    per train, of 257, shorter or looser ones on one: the same trains to the order of the FP64 sums.
+    In the window 0.5 <= K/S0 <= 1.5 each side's prices are within a few times the tolerance of the
+    grid's own (the undamping there is below 3^1.5), so the two lie within ten times it."""
+    import cm_workloads as W
+    probs = W.vg_batch(4, n=n) + W.heston_batch(4, seed=5, n=n)
+    u = [W.window_strided(p, 48) for p in probs]
+    k = min(len(v) for v in u)
+    got = []
+    for batch in (256, 257):
+        pr = cm.SfftPricer([probs[i % 8] for i in range(batch)], cm.CM_C128, tol=tol, cap=32)
+        s = torch.from_numpy(np.stack([u[i % 8][:k] for i in range(batch)])).cuda()
+        got.append(pr.run(s).cpu().numpy())
+        assert not any(v.any() for v in pr.statuses().values())
+        assert np.array_equal(got[-1][:8], got[-1][8:16])
+    assert np.abs(got[0] - got[1][:256]).max() <= 10 * tol * probs[0].S0
