@@ -42,6 +42,7 @@ namespace {
 constexpr int NT_MAX = 1024;   // threads per FFT workgroup (at most)
 constexpr size_t DENSE_PROB_BYTES = 512;  // workspace slot per problem
 constexpr int MAX_CHUNK = 32768;
+constexpr int CUS = 256;
 
 template <typename T> struct fr;
 template <> struct fr<float2> {
@@ -124,14 +125,29 @@ __host__ inline size_t fft_min_ws_bytes(int n, int dtype, bool gather, int batch
   return o;
 }
 
-// Passes: the first takes as much as leaves the others 6 bits (a radix-2 pass moves as many bytes
-// as any other: the third pass of n = 26 was one of two bits and took 950 of 1370 us), the rest is
-// split evenly. A group's instances are what fits the workspace.
+// Passes. The first takes as much as leaves the others 6 bits (a radix-2 pass moves as many bytes as
+// any other: the third pass of n = 26 was one of two bits and took 950 of 1370 us), up to 11 bits, and
+// beyond them no more than bring the next pass down to 8 bits (CM_C64) or 9; the rest is split
+// evenly. A larger first pass is a workgroup of up to 1024 threads with a CU to itself, few of them,
+// and evaluates its share of G in 128 registers a thread (at 2^13 points of CM_C128 112 of them spill):
+// where G fills the grid, that is most of the call. 16 grids, 300 strikes, as large a first pass as
+// leaves 6 bits -> this rule (the full-length transform in brackets): Variance Gamma n = 20 CM_C128
+// 1029 -> 529 us (603), n = 21 1963 -> 886 (1141), n = 22 3395 -> 1903 (2176), CM_C64 n = 20 233 -> 162
+// (270), n = 21 421 -> 280 (382); where G is a sliver, Heston n = 20 CM_C128 178 -> 186 (350), n = 21
+// CM_C64 231 -> 236 (358). n = 24 CM_C128 needs 13 and 10 bits for two passes and keeps 2^13.
+// A grid of the largest single pass takes two while there are fewer grids than CUs: one Variance Gamma
+// grid of n = 14 in CM_C128 takes 47 us (141 in one pass, 84 of the full-length transform in two),
+// 1000 Black-Scholes grids 90 us in one and 250 in two.
+// A group's instances are what fits the workspace.
 __host__ inline FftPlan make_plan(int n, int dtype, bool gather, int batch, size_t ws_bytes) {
   FftPlan p;
   p.n = n;
   const int nb = n - 1, f = first_radix_bits(dtype), g = later_radix_bits(dtype);
-  int b0 = nb <= f ? nb : nb - 6 < f ? nb - 6 : f;
+  int b0 = nb;
+  if (nb > f || (nb == f && batch < CUS)) {
+    b0 = nb <= 18 ? (nb - 6 < 11 ? nb - 6 : 11) : nb - (dtype == CM_C64 ? 8 : 9);
+    if (b0 > f) b0 = f;
+  }
   p.logr[0] = b0;
   int rem = nb - b0;
   const int k = rem == 0 ? 0 : rem <= g ? 1 : (rem + g - 2) / (g - 1);

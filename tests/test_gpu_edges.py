@@ -241,3 +241,26 @@ def test_sweeps_either_side_of_the_four_wave_rule(n, tol):
         assert not any(v.any() for v in pr.statuses().values())
         assert np.array_equal(got[-1][:8], got[-1][8:16])
     assert np.abs(got[0] - got[1][:256]).max() <= 10 * tol * probs[0].S0
+
+
+# ------------------------------------------------------------------ dense path
+
+@pytest.mark.parametrize("dtype,n", [(cm.CM_C64, 15), (cm.CM_C128, 14)])
+@pytest.mark.parametrize("model", ["heston", "vg"])
+def test_dense_largest_single_pass_either_side(dtype, n, model):
+    """The largest grid of one pass takes two while there are fewer than 256 grids. Near the money
+    (0.5 <= K/S0 <= 1.5, undamping below 3^1.5) the two differ by the rounding of two transforms: at most
+    4 units in the last place per level of each, of sums no larger than a few times the largest price."""
+    import cm_workloads as W
+    probs = W.heston_batch(3, seed=2, n=n) if model == "heston" else W.vg_batch(3, n=n)
+    u = [W.window_strided(p, 200) for p in probs]
+    k = min(len(v) for v in u)
+    got = []
+    for batch in (255, 256):
+        s = torch.from_numpy(np.stack([u[i % 3][:k] for i in range(batch)])).cuda()
+        p, st = cm.dense_prices([probs[i % 3] for i in range(batch)], dtype, s)
+        assert int(st.abs().sum()) == 0
+        got.append(p.double())
+        assert torch.equal(p[:3], p[3:6])
+    eps = 2.0 ** (-24 if dtype == cm.CM_C64 else -53)
+    assert float((got[0][:3] - got[1][:3]).abs().max()) <= 8 * n * 3 ** 1.5 * 3 * eps * float(got[0].abs().max())
