@@ -43,6 +43,7 @@ constexpr int NT_MAX = 1024;   // threads per FFT workgroup (at most)
 constexpr size_t DENSE_PROB_BYTES = 512;  // workspace slot per problem
 constexpr int MAX_CHUNK = 32768;
 constexpr int CUS = 256;
+constexpr int PREP_ONE = 3000;
 
 template <typename T> struct fr;
 template <> struct fr<float2> {
@@ -258,10 +259,20 @@ template <typename T> constexpr int fft_threads(int b) {
   const int t = (1 << b) / pts_per_thread<T>;
   return t < 64 ? 64 : t > NT_MAX ? NT_MAX : t;
 }
-// of pass 1 with 2^b points: eight points a thread at most, for the evaluation of G
+// of pass 1 with 2^b points: eight points a thread at most, for the evaluation of G; 2^8 points of
+// CM_C64 a pair of inputs a thread (4000 Heston grids of n = 9 139 us, with two or three pairs 152)
 template <typename T> constexpr int first_threads(int b) {
+  if (sizeof(T) == 8 && b == 8) return 192;
   const int t = (1 << b) / 8;
   return t < 64 ? 64 : t > NT_MAX ? NT_MAX : t;
+}
+// Up to WIDE_GRIDS grids of 2^8 to 2^10 points in one pass are bound by the latency of the few
+// evaluations in turn on each thread (16 values of the integrand at 2^9 points): their workgroups
+// have a thread per value, as far as 1024 go, four of them to a pair of inputs.
+constexpr int WIDE_B0 = 8, WIDE_B = 10, WIDE_GRIDS = 512;
+constexpr int wide_threads(int b) {
+  const int t = 2 * (1 << b) + 64;
+  return t > NT_MAX ? NT_MAX : t;
 }
 
 // Twiddles t w^r, r < R, with w = exp(-2 pi i f) and t = exp(-2 pi i f0) (f, f0 turn fractions;
@@ -479,6 +490,26 @@ __device__ __forceinline__ T g_pair(const DenseProb<T> &d, int64_t j, T *other) 
   if (other) *other = fr<T>::mk(0.5 * (s.x - e.x), 0.5 * (e.y - s.y));
   return fr<T>::mk(0.5 * (s.x + e.x), 0.5 * (s.y + e.y));
 }
+// The same on four neighbouring lanes, one value of z each (q = lane mod 4): lane 0 returns G_j, lane 1
+// G_{h-j}. Every lane of the wave takes part, with the j of its four.
+template <typename T>
+__device__ __forceinline__ T g_quad(const DenseProb<T> &d, int64_t j, int q) {
+  const int64_t h = (int64_t)1 << (d.c.n - 1), M = 2 * h;
+  const bool out = j >= d.side && j <= h - d.side;
+  double2 z = cmk(0.0, 0.0);
+  if (!out) z = z_at<T>(d, q == 0 ? j : q == 1 ? M - j : q == 2 ? j + h : h - j);
+  if (q & 1) z = cconj(z);
+  const double2 o = cmk(__shfl_xor(z.x, 1, 64), __shfl_xor(z.y, 1, 64));
+  const double2 ab = cadd(z, o);   // a on lanes 0 and 1, b on 2 and 3
+  const double2 c = cmk(__shfl_xor(ab.x, 2, 64), __shfl_xor(ab.y, 2, 64));
+  const double2 a = q < 2 ? ab : c, b = q < 2 ? c : ab;
+  const bool far = 2 * j > h;
+  double2 w = fr<double2>::cis_neg(ldexp((double)(far ? h - j : j), -d.c.n));
+  if (far) w.x = -w.x;
+  const double2 e = cmul(cmk(-w.y, w.x), csub(a, b)), s = cadd(a, b);
+  if (out) return fr<T>::mk(0.0, 0.0);
+  return q & 1 ? fr<T>::mk(0.5 * (s.x - e.x), 0.5 * (e.y - s.y)) : fr<T>::mk(0.5 * (s.x + e.x), 0.5 * (s.y + e.y));
+}
 template <typename T> __device__ __forceinline__ T g_at(const DenseProb<T> &d, int64_t j) {
   return g_pair<T>(d, j, nullptr);
 }
@@ -574,12 +605,13 @@ template <typename T> struct PriceDst {   // last pass: readout scalars, two pri
   }
 };
 
-// Per problem: constants, and the numerical support of x. Four wavefronts per problem (one took
-// their four quarters in turn: 24 us of a small call) evaluate |h| at v = +-2^{q/4 - 4}, q < 256, finds the first q from which five consecutive
-// points lie below thr |h(0)|, and keeps indices with |v| < 2 v_q. A problem that fails
-// its checks keeps the whole range and is marked bad.
-template <typename T>
-__global__ __launch_bounds__(256) void k_fft_prepare(const cm_problem *__restrict__ prob, int batch, int n, double thr,
+// Per problem: constants, and the numerical support of x. W wavefronts per problem evaluate |h| at
+// v = +-2^{q/4 - 4}, q < 256, find the first q from which five consecutive points lie below
+// thr |h(0)|, and keep indices with |v| < 2 v_q. A problem that fails its checks keeps the whole
+// range and is marked bad. Four waves, where one takes their quarters in turn (24 us of a small call);
+// one from PREP_ONE problems on, which fill the chip either way (4000 Heston grids of n = 1: 10 us less).
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W) void k_fft_prepare(const cm_problem *__restrict__ prob, int batch, int n, double thr,
                                                      DenseProb<T> *__restrict__ out, int32_t *__restrict__ status) {
   __shared__ uint64_t below[4];
   const int b = blockIdx.x;
@@ -593,11 +625,15 @@ __global__ __launch_bounds__(256) void k_fft_prepare(const cm_problem *__restric
     const CfModel<double> m = make_model<double>(pr);
     const cx<double> h0 = h_centered<double>(m, 0.0);
     const double lim = thr * sqrt(h0.x * h0.x + h0.y * h0.y);
-    const double v = exp2(0.25 * (int)threadIdx.x - 4.0);
-    const cx<double> hp = h_centered<double>(m, v), hm = h_centered<double>(m, -v);
-    const double a = fmax(sqrt(hp.x * hp.x + hp.y * hp.y), sqrt(hm.x * hm.x + hm.y * hm.y));
-    const uint64_t mask = __ballot(a < lim);
-    if ((threadIdx.x & 63) == 0) below[threadIdx.x >> 6] = mask;
+#pragma unroll
+    for (int k = 0; k < 4; k += W) {
+      const int w = k + (int)(threadIdx.x >> 6);
+      const double v = exp2(0.25 * (64 * w + (int)(threadIdx.x & 63)) - 4.0);
+      const cx<double> hp = h_centered<double>(m, v), hm = h_centered<double>(m, -v);
+      const double a = fmax(sqrt(hp.x * hp.x + hp.y * hp.y), sqrt(hm.x * hm.x + hm.y * hm.y));
+      const uint64_t mask = __ballot(a < lim);
+      if ((threadIdx.x & 63) == 0) below[w] = mask;
+    }
     __syncthreads();
     // the first q whose five points from q on all lie below: shifted masks, word by word (q + 4 <= 255)
     int qcut = -1;
@@ -661,10 +697,10 @@ template <typename T> struct PrunedSrc {
 // inputs of either side that a pruned start keeps in LDS, at most
 template <typename T> constexpr int PRUNE_MAX = sizeof(T) == 8 ? 1024 : 512;
 
-template <typename T, int LOGR, int REM, class Dst>
+template <typename T, int LOGR, int REM, int NT, class Dst>
 __device__ __forceinline__ void first_pass_pruned(T *a, const DenseProb<T> &d, int64_t item, int64_t T_items,
                                                   const Dst &dst) {
-  constexpr int NT = first_threads<T>(LOGR), n = 1 << REM, L = 1 << LOGR;
+  constexpr int n = 1 << REM, L = 1 << LOGR;
   static_assert(n <= PRUNE_MAX<T>, "LDS behind the FFT buffer");
   T *ab = a + pidx(L) + 1;
   if (T_items == 1) {   // input L - e is input e's partner
@@ -684,9 +720,9 @@ __device__ __forceinline__ void first_pass_pruned(T *a, const DenseProb<T> &d, i
 
 // Chooses the latest start that the problem's support allows, counted in remaining bits: one, two
 // or three register stages.
-template <typename T, int LOGR, class Dst>
+template <typename T, int LOGR, bool WIDE, class Dst>
 __device__ __forceinline__ void first_pass(T *a, const DenseProb<T> &d, int64_t item, int64_t T_items, const Dst &dst) {
-  constexpr int RB = pts_per_thread<T> >= 16 ? 4 : 3, NT = first_threads<T>(LOGR);
+  constexpr int RB = pts_per_thread<T> >= 16 ? 4 : 3, NT = WIDE ? wide_threads(LOGR) : first_threads<T>(LOGR);
   if constexpr (LOGR == 0) {
     if (threadIdx.x == 0) {
       const T g = g_at<T>(d, 0);
@@ -697,14 +733,23 @@ __device__ __forceinline__ void first_pass(T *a, const DenseProb<T> &d, int64_t 
     const int64_t E = (d.side + T_items - 1) / T_items;   // more than L / 2 when nothing is known
     constexpr int R1 = RB, R2 = 2 * RB - 2, R3 = 2 * RB, R4 = RB == 4 ? 10 : 9;
     if constexpr (LOGR > R1)
-      if (E <= (1 << R1)) return first_pass_pruned<T, LOGR, R1>(a, d, item, T_items, dst);
+      if (E <= (1 << R1)) return first_pass_pruned<T, LOGR, R1, NT>(a, d, item, T_items, dst);
     if constexpr (LOGR >= 12)
-      if (E <= (1 << R2)) return first_pass_pruned<T, LOGR, R2>(a, d, item, T_items, dst);
+      if (E <= (1 << R2)) return first_pass_pruned<T, LOGR, R2, NT>(a, d, item, T_items, dst);
     if constexpr (LOGR > R3)
-      if (E <= (1 << R3)) return first_pass_pruned<T, LOGR, R3>(a, d, item, T_items, dst);
+      if (E <= (1 << R3)) return first_pass_pruned<T, LOGR, R3, NT>(a, d, item, T_items, dst);
     if constexpr (LOGR > R4)
-      if (E <= (1 << R4)) return first_pass_pruned<T, LOGR, R4>(a, d, item, T_items, dst);
-    if (T_items == 1) {
+      if (E <= (1 << R4)) return first_pass_pruned<T, LOGR, R4, NT>(a, d, item, T_items, dst);
+    if constexpr (WIDE) {   // one pass
+      constexpr int L = 1 << LOGR;
+      const int q = threadIdx.x & 3;
+      for (int e0 = 0; e0 <= L / 2; e0 += NT / 4) {
+        const int e = e0 + (int)(threadIdx.x >> 2);
+        const T v = g_quad<T>(d, e <= L / 2 ? e : 0, q);
+        if (q == 0 && e <= L / 2) a[pidx(e)] = v;
+        if (q == 1 && e > 0 && e < L / 2) a[pidx(L - e)] = v;
+      }
+    } else if (T_items == 1) {
       constexpr int L = 1 << LOGR;
       for (int e = threadIdx.x; e <= L / 2; e += NT) {
         T o;
@@ -738,10 +783,10 @@ template <typename T> struct PassDst {
 // Pass 1: one work item (blockIdx.x) per workgroup; G is generated (only lanes inside the support
 // evaluate the characteristic function), then transformed. Prices go out at once when this is
 // the only pass and no strikes are chosen.
-template <typename T, int LOGR>
-__global__ __launch_bounds__(first_threads<T>(LOGR)) void k_fft_first(const DenseProb<T> *__restrict__ dprob, int inst0,
-                                                                    int n, T *__restrict__ out,
-                                                                    typename price_t<T>::type *__restrict__ prices) {
+template <typename T, int LOGR, bool WIDE>
+__global__ __launch_bounds__(WIDE ? wide_threads(LOGR) : first_threads<T>(LOGR)) void k_fft_first(
+    const DenseProb<T> *__restrict__ dprob, int inst0, int n, T *__restrict__ out,
+    typename price_t<T>::type *__restrict__ prices) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T *a = (T *)lds_raw;
   const int64_t N = (int64_t)1 << (n - 1);
@@ -749,7 +794,7 @@ __global__ __launch_bounds__(first_threads<T>(LOGR)) void k_fft_first(const Dens
   const int64_t item = blockIdx.x, T_items = N >> LOGR;
   const PassDst<T> dst{{out + (int64_t)blockIdx.y * N, item, 1, LOGR},
                        {prices ? prices + (int64_t)blockIdx.y * 2 * N : nullptr, &d->c, item, 1, LOGR, d->bad}};
-  first_pass<T, LOGR>(a, *d, item, T_items, dst);
+  first_pass<T, LOGR, WIDE>(a, *d, item, T_items, dst);
 }
 
 // Later passes: 16 or 8 consecutive work items per workgroup, loaded straight into the
@@ -777,8 +822,12 @@ __global__ __launch_bounds__(fft_threads<T>(LOGR + log_cols(sizeof(T) == 8 ? CM_
 
 // Host-side tables of the instantiations, indexed by radix bits.
 template <typename T, int... B>
-static constexpr std::array<decltype(&k_fft_first<T, 1>), sizeof...(B)> first_table(std::integer_sequence<int, B...>) {
-  return {&k_fft_first<T, B>...};
+static constexpr std::array<decltype(&k_fft_first<T, 1, false>), sizeof...(B)> first_table(std::integer_sequence<int, B...>) {
+  return {&k_fft_first<T, B, false>...};
+}
+template <typename T, int... B>
+static constexpr std::array<decltype(&k_fft_first<T, WIDE_B, true>), sizeof...(B)> wide_table(std::integer_sequence<int, B...>) {
+  return {&k_fft_first<T, WIDE_B0 + B, true>...};
 }
 template <typename T, int... B>
 static constexpr std::array<decltype(&k_fft_next<T, 1>), sizeof...(B)> next_table(std::integer_sequence<int, B...>) {
@@ -827,23 +876,30 @@ static cm_status fft_run(const cm_problem *prob, int batch, int n, const int64_t
   if (p.bufs > 1) buf[1] = (T *)(w + al256f(sizeof(T) * (size_t)N * p.chunk));
   // cut-off of |psi| relative to |psi(0)|, far below the storage precision
   const double thr = dtype == CM_C64 ? 1e-16 : 1e-32;
-  hipLaunchKernelGGL(k_fft_prepare<T>, dim3(batch), dim3(256), 0, s, prob, batch, n, thr, dp, status);
+  if (batch < PREP_ONE)
+    hipLaunchKernelGGL((k_fft_prepare<T, 4>), dim3(batch), dim3(256), 0, s, prob, batch, n, thr, dp, status);
+  else
+    hipLaunchKernelGGL((k_fft_prepare<T, 1>), dim3(batch), dim3(64), 0, s, prob, batch, n, thr, dp, status);
   CM_LAUNCH_CHECK();
   constexpr int FB = first_radix_bits(dtype), NB = later_radix_bits(dtype);
   static constexpr auto kfirst = first_table<T>(std::make_integer_sequence<int, FB + 1>{});
+  static constexpr auto kwide = wide_table<T>(std::make_integer_sequence<int, WIDE_B - WIDE_B0 + 1>{});
   static constexpr auto knext = next_table<T>(std::make_integer_sequence<int, NB>{});
   const int lr0 = p.logr[0];
   if (lr0 < 0 || lr0 > FB) return CM_E_UNSUPPORTED;
   for (int ps = 1; ps < p.npass; ++ps)
     if (p.logr[ps] < 1 || p.logr[ps] > NB) return CM_E_UNSUPPORTED;
   const size_t lds0 = first_lds_bytes<T>(lr0);
-  CM_HIP_CHECK(cm_allow_lds(kfirst[lr0], lds0));
+  const bool wide = p.npass == 1 && lr0 >= WIDE_B0 && lr0 <= WIDE_B && batch <= WIDE_GRIDS;
+  const auto first = wide ? kwide[lr0 - WIDE_B0] : kfirst[lr0];
+  const int nt0 = wide ? wide_threads(lr0) : first_threads<T>(lr0);
+  CM_HIP_CHECK(cm_allow_lds(first, lds0));
   for (int ps = 1; ps < p.npass; ++ps)
     CM_HIP_CHECK(cm_allow_lds(knext[p.logr[ps] - 1], lds_bytes(p.logr[ps], 1 << log_cols(dtype, p.logr[ps]), sizeof(T))));
   for (int inst0 = 0; inst0 < batch; inst0 += p.chunk) {
     const int cnt = (batch - inst0) < p.chunk ? (batch - inst0) : p.chunk;
     P *dstp = (P *)prices + (int64_t)inst0 * M;   // where the last pass writes prices
-    hipLaunchKernelGGL(kfirst[lr0], dim3((unsigned)(N >> lr0), cnt), dim3(first_threads<T>(lr0)), lds0, s, dp, inst0, n,
+    hipLaunchKernelGGL(first, dim3((unsigned)(N >> lr0), cnt), dim3(nt0), lds0, s, dp, inst0, n,
                        buf[0], p.npass == 1 && !gather ? dstp : (P *)nullptr);
     CM_LAUNCH_CHECK();
     int64_t plen = (int64_t)1 << lr0;

@@ -264,3 +264,20 @@ def test_dense_largest_single_pass_either_side(dtype, n, model):
         assert torch.equal(p[:3], p[3:6])
     eps = 2.0 ** (-24 if dtype == cm.CM_C64 else -53)
     assert float((got[0][:3] - got[1][:3]).abs().max()) <= 8 * n * 3 ** 1.5 * 3 * eps * float(got[0].abs().max())
+
+
+@pytest.mark.parametrize("dtype", [cm.CM_C64, cm.CM_C128])
+@pytest.mark.parametrize("n,few,many", [(9, 512, 513), (10, 512, 513), (11, 512, 513), (10, 1, 513), (9, 2999, 3000)])
+def test_dense_small_grids_either_side(dtype, n, few, many):
+    """Up to 512 grids of n = 9 to 11 have a thread per value of the integrand, from 3000 problems on one
+    wave finds a support: the same values and transforms, to
+    the rounding that the test above allows (the compiler may fuse the products differently)."""
+    import cm_workloads as W
+    probs = [W.heston_batch(1, seed=2, n=n)[0], W.vg_batch(1, n=n)[0], W.bs_batch(1, n=n)[0]]
+    every = [cm.dense_prices([probs[i % 3] for i in range(max(b, 3))], dtype) for b in (few, many)]
+    a, b = every[0][0][:3].double(), every[1][0][:3].double()
+    assert int(every[0][1].abs().sum()) == 0 and int(every[1][1].abs().sum()) == 0
+    for i, p in enumerate(probs):
+        u = torch.from_numpy(W.window_strided(p, 100)).cuda()
+        eps = 2.0 ** (-24 if dtype == cm.CM_C64 else -53)
+        assert float((a[i][u] - b[i][u]).abs().max()) <= 8 * n * 3 ** 1.5 * 3 * eps * float(a[i][u].abs().max())
