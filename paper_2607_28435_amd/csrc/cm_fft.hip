@@ -260,7 +260,8 @@ template <typename T> constexpr int fft_threads(int b) {
   return t < 64 ? 64 : t > NT_MAX ? NT_MAX : t;
 }
 // of pass 1 with 2^b points: eight points a thread at most, for the evaluation of G; 2^8 points of
-// CM_C64 a pair of inputs a thread (4000 Heston grids of n = 9 139 us, with two or three pairs 152)
+// CM_C64 a pair of inputs a thread (4000 Heston grids of n = 9 139 us, with two or three pairs 152; 119 with
+// one wave per problem in k_fft_prepare as well)
 template <typename T> constexpr int first_threads(int b) {
   if (sizeof(T) == 8 && b == 8) return 192;
   const int t = (1 << b) / 8;
@@ -609,7 +610,7 @@ template <typename T> struct PriceDst {   // last pass: readout scalars, two pri
 // v = +-2^{q/4 - 4}, q < 256, find the first q from which five consecutive points lie below
 // thr |h(0)|, and keep indices with |v| < 2 v_q. A problem that fails its checks keeps the whole
 // range and is marked bad. Four waves, where one takes their quarters in turn (24 us of a small call);
-// one from PREP_ONE problems on, which fill the chip either way (4000 Heston grids of n = 1: 10 us less).
+// one from PREP_ONE problems on, which fill the chip either way (4000 grids of n = 4: 1.18 times as fast).
 template <typename T, int W>
 __global__ __launch_bounds__(64 * W) void k_fft_prepare(const cm_problem *__restrict__ prob, int batch, int n, double thr,
                                                      DenseProb<T> *__restrict__ out, int32_t *__restrict__ status) {
@@ -625,14 +626,18 @@ __global__ __launch_bounds__(64 * W) void k_fft_prepare(const cm_problem *__rest
     const CfModel<double> m = make_model<double>(pr);
     const cx<double> h0 = h_centered<double>(m, 0.0);
     const double lim = thr * sqrt(h0.x * h0.x + h0.y * h0.y);
-#pragma unroll
-    for (int k = 0; k < 4; k += W) {
-      const int w = k + (int)(threadIdx.x >> 6);
-      const double v = exp2(0.25 * (64 * w + (int)(threadIdx.x & 63)) - 4.0);
+    auto scan = [&](int w, int q) {
+      const double v = exp2(0.25 * q - 4.0);
       const cx<double> hp = h_centered<double>(m, v), hm = h_centered<double>(m, -v);
       const double a = fmax(sqrt(hp.x * hp.x + hp.y * hp.y), sqrt(hm.x * hm.x + hm.y * hm.y));
       const uint64_t mask = __ballot(a < lim);
       if ((threadIdx.x & 63) == 0) below[w] = mask;
+    };
+    if constexpr (W == 4) {
+      scan(threadIdx.x >> 6, threadIdx.x);
+    } else {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) scan(w, 64 * w + (int)(threadIdx.x & 63));
     }
     __syncthreads();
     // the first q whose five points from q on all lie below: shifted masks, word by word (q + 4 <= 255)
