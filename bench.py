@@ -796,14 +796,17 @@ def main():
     M = 2 ** args.n
     dense_gps = 1.0 / dense_s
     # half-length transform: pass-1 write, pass-2 read (M / 2 complex points) + price write
-    dense_bytes = 4 * M + (4 * M + 4 * M) if args.n > 15 else 4 * M
+    dense_bytes = 4 * M + (4 * M + 4 * M) if args.n > (14 if nd < 256 else 15) else 4 * M
     dense_gbs = dense_bytes / (dense_ms_ev * 1e-3) / 1e9
-    # the same grids four instances per launch group (a workspace sized for it): the pass
-    # buffers (4 x 134 MB at n = 24) exceed the 256 MB Infinity Cache, so the intermediate
-    # makes a real DRAM round trip, unlike one instance per launch
-    group = 4
+    # A launch group is as many grids as the workspace has pass buffers for, M / 2 complex points each
+    # (the default workspace holds three; the group is the same to the byte of a few constants). The
+    # same grids again with eight to a group: buffers that exceed the 256 MB Infinity Cache, so that
+    # the intermediate makes a real DRAM round trip
+    buf = 4 * M
+    need = cm.cm_workspace_bytes(cm.CM_OP_FFT_PRICE, nd, args.n, 0, cm.CM_C64)
+    group, group_dram = min(nd, max(1, (need - 512 * nd) // buf)), min(nd, 8)
     dws4 = cm.Workspace(dev)
-    dws4.get(cm.cm_workspace_bytes(cm.CM_OP_FFT_PRICE, nd, args.n, 0, cm.CM_C64) + 8 * M * (group - 1))
+    dws4.get(need + buf * max(0, group_dram - group))
     cm.cm_fft_price(dprob, nd, args.n, cm.CM_C64, None, 0, dprices, dstat, dws4)
     torch.cuda.synchronize()
     e0.record(stream)
@@ -932,13 +935,16 @@ def main():
                            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dense_gbs / HBM_PEAK_GBS,
                            "algorithmic_bytes": dense_bytes, "traffic": profiled_traffic("dense", FFT_SOURCES),
                            "traffic_per": PROFILED_TRAFFIC["dense"]["per"],
-                           "note": "one instance per launch: its 134 MB intermediate stays in the 256 MB Infinity "
-                                   "Cache between the passes"},
-        "dense_dram_roofline": {"kernel": "k_fft_first + k_fft_next, 4 instances per launch group", "bound": "hbm",
+                           "group": group,
+                           "note": f"{group} grids per launch group: their {group * buf / 1e6:.0f} MB of pass buffers "
+                                   "against 256 MB of Infinity Cache"},
+        "dense_dram_roofline": {"kernel": f"k_fft_first + k_fft_next, {group_dram} grids per launch group", "bound": "hbm",
                                 "achieved": dense_dram_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                 "frac": dense_dram_gbs / HBM_PEAK_GBS, "algorithmic_bytes": dense_bytes,
                                 "ms_per_grid": dense_dram_ms,
-                                "note": "pass buffers of 4 instances (537 MB) exceed the Infinity Cache: DRAM-resident"},
+                                "group": group_dram,
+                                "note": f"{group_dram * buf / 1e6:.0f} MB of pass buffers exceed the Infinity Cache: "
+                                        "DRAM-resident"},
     }
     if not args.no_cpu_baseline:
         rec, priced = cpu_baseline(probs)
