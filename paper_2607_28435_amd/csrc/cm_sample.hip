@@ -22,10 +22,12 @@
 // k_sample is bound by the FP64 multiply-adds it executes and, with three waves a SIMD, by the
 // scalar loads between them; so what counts is how much of the work is padding and how far the
 // loads run ahead. Blocks of 4 made 1.43 times the work out of a bond of 10. Up to bonds of 16
-// the padding is to 2, bonds up to 12 have an instantiation that fits four waves, and the two
-// largest sizes of each have branch-free code. 512 Heston trains of n = 24 (bonds <= 10), 4096
-// shots: 2.53 -> 1.93 ms. 256 trains of n = 20 by their bond, 4096 shots, the whole call: 6:
-// 0.68 -> 0.51 ms, 8: 0.70 -> 0.71, 10: 1.64 -> 1.06, 12: 1.65 -> 1.31, 14: 2.54 -> 1.92,
+// the padding is to 2, bonds up to 4, 8, 12 and 16 have an instantiation each, and the two largest even
+// sizes of each have branch-free code. Up to 4 it fits eight waves a SIMD, up to 8 and 12 it is held
+// to four, up to 16 to three (at 12 and 16 that spills a few registers: 24 and 6). 512 Heston trains of
+// n = 24 (bonds <= 10), 4096 shots: 2.53 -> 1.93 ms. 64 trains of n = 20, 4096 shots, the whole call,
+// in us (4 x 4 blocks in front): bonds of 2 117 -> 83, 4 123 -> 118 (128 in the instantiation for 8), 6
+// 231 -> 176, 8 239 -> 237, 10 559 -> 332, 12 573 -> 417. 256 trains, ms: 14 2.54 -> 1.92,
 // 16: 2.57 -> 2.31. Above 16 the same blocks of 2 are 9 % slower than whole ones (24: 14.2 against
 // 12.7 ms; one wave a SIMD, and the remainder is a small part): those keep blocks of 4. Orthonormal
 // rows in place of the environments (a mass is then ||w||^2: a third of the work less) took
@@ -246,7 +248,7 @@ __device__ __forceinline__ double continuation(const double2 *v, const double2 *
 }
 
 template <int RM>
-__global__ __launch_bounds__(SMP_WG, RM <= 8 ? 4 : RM <= 12 ? 4 : RM <= 16 ? 3 : 1) void k_sample(TTView y, const double2 *__restrict__ ws, int RS, int n_max,
+__global__ __launch_bounds__(SMP_WG, RM <= 4 ? 8 : RM <= 12 ? 4 : RM <= 16 ? 3 : 1) void k_sample(TTView y, const double2 *__restrict__ ws, int RS, int n_max,
                                                    int64_t inst_stride, const double *__restrict__ norm2,
                                                    const double *__restrict__ uni, int ustride, int R,
                                                    int64_t *__restrict__ out, int rm_lo) {
@@ -296,7 +298,6 @@ __global__ __launch_bounds__(SMP_WG, RM <= 8 ? 4 : RM <= 12 ? 4 : RM <= 16 ? 3 :
         const double2 *Yb = Y + bit * pb;
         if (RM <= PAD2_MAX && pa == RM - 2 && pb == RM - 2) q = continuation<RM>(v, Yb, E, RM - 2, RM - 2, w);
         else if (RM <= PAD2_MAX && pa == RM && pb == RM) q = continuation<RM>(v, Yb, E, RM, RM, w);
-        else if (RM == 8 && pa == 4 && pb == 4) q = continuation<RM>(v, Yb, E, 4, 4, w);
         else q = continuation<RM>(v, Yb, E, pa, pb, w);
         if (bit) idx |= (int64_t)1 << t;
         more = lim >= q;
@@ -352,7 +353,8 @@ extern "C" cm_status cm_sample_outcomes(const cm_tt_batch *y, const double *unif
 #define CM_SAMPLE_LAUNCH(RM, LO)                                                                         \
   hipLaunchKernelGGL((k_sample<RM>), grid, dim3(SMP_WG), 0, s, v, slab, RS, nm, inst_stride, norm2, uniforms, us, R, \
                      out, LO)
-  CM_SAMPLE_LAUNCH(8, 0);
+  CM_SAMPLE_LAUNCH(4, 0);
+  if (y->cap_rank > 4) CM_SAMPLE_LAUNCH(8, 4);
   if (y->cap_rank > 8) CM_SAMPLE_LAUNCH(12, 8);
   if (y->cap_rank > 12) CM_SAMPLE_LAUNCH(16, 12);
   if (y->cap_rank > 16) CM_SAMPLE_LAUNCH(32, 16);
