@@ -23,8 +23,9 @@
 //     where |psi| has decayed below a per-problem cutoff far under the storage precision (found
 //     once per problem by k_fft_prepare), which skips the characteristic function outside the
 //     integrand's numerical support and the stages that would only spread zeros.
-//   - Later passes handle 16 consecutive work items per workgroup (8 at the largest radix), so
-//     every global load and store moves 64 to 128 consecutive bytes.
+//   - Later passes handle 16 consecutive work items per workgroup up to 2^9 points (CM_C64) or 2^8, 8 and
+//     then 4 at the two radices above, so a load or store moves 128 (CM_C64) or 256 consecutive bytes,
+//     32 or 64 at the largest radix.
 //   - The last pass multiplies by the readout scalars and stores prices; in FP64 each price
 //     takes its log-strike from the error-free grid sum (1e-15 NRMSE on the paper grid up
 //     to n = 30). When strikes are chosen it stores g, and the gather prices those alone.
@@ -62,11 +63,6 @@ template <> struct fr<float2> {
     sincospif(xf, &s, &c);
     return make_float2(fmaf(-s, d, c), fmaf(c, d, s));
   }
-  // e^{-alpha k} / (s pi) for the readout: FP64 exponent split, FP32 mantissa
-  __device__ __forceinline__ static double escale(double z) {   // 2^z
-    const double zi = floor(z);
-    return ldexp((double)exp2f((float)(z - zi)), (int)zi);
-  }
 };
 template <> struct fr<double2> {
   using R = double;
@@ -80,7 +76,6 @@ template <> struct fr<double2> {
     sincospi(-2.0 * f, &s, &c);
     return cmk(c, s);
   }
-  __device__ __forceinline__ static double escale(double z) { return exp2(z); }
 };
 
 // cos(2 pi m / 16) for any integer m
@@ -101,6 +96,7 @@ struct FftPlan {
 
 __host__ __device__ constexpr int first_radix_bits(int dtype) { return dtype == CM_C64 ? 14 : 13; }
 __host__ __device__ constexpr int later_radix_bits(int dtype) { return dtype == CM_C64 ? 11 : 10; }
+constexpr int LATER_MIN_BITS = 5;   // make_plan leaves later passes 5 (CM_C128) or 6 bits at least
 // work items per workgroup after the first pass: 16, fewer where two workgroups could not share a
 // CU (2^13 points of CM_C64, 2^12 of CM_C128 are 70 KB of LDS)
 __host__ __device__ constexpr int log_cols(int dtype, int logr) {
@@ -279,8 +275,11 @@ constexpr int wide_threads(int b) {
 // Twiddles t w^r, r < R, with w = exp(-2 pi i f) and t = exp(-2 pi i f0) (f, f0 turn fractions;
 // HAS_T false: t = 1), in FP64 and rounded once at the end. The r-th power of a rounded w is off
 // by r ulps, and the integrand's negative frequencies sit at the largest r, so the upper half goes
-// down from w^R, which has a fraction of its own (powers in FP32 took a 2^26-point grid's error
-// from 3.8e-7 to 1.2e-6). FP64 multiplies issue at the rate of FP32 ones.
+// down from w^R, which has a fraction of its own (powers in FP32 tripled the error of a Heston grid of
+// n = 26). FP64 multiplies issue at the rate of FP32 ones. Error of all prices against FP64 (relative,
+// 2-norm; geometric mean over 10 to 16 Heston grids within a factor e^pi of the spot, the full-length
+// transform in brackets): n = 16 7.9e-7 (8.5e-7), n = 20 8.0e-7 (8.5e-7), n = 24 8.2e-7 (8.6e-7), n = 26
+// 9.6e-7 (9.3e-7); one grid may be a quarter above or below the other transform's.
 template <typename T, int R, bool HAS_T> __device__ __forceinline__ void twiddles(double f, double f0, T *tw) {
   double2 pw[R / 2 + 1];
   pw[0] = cmk(1.0, 0.0);
@@ -802,7 +801,7 @@ __global__ __launch_bounds__(WIDE ? wide_threads(LOGR) : first_threads<T>(LOGR))
   first_pass<T, LOGR, WIDE>(a, *d, item, T_items, dst);
 }
 
-// Later passes: 16 or 8 consecutive work items per workgroup, loaded straight into the
+// Later passes: 16, 8 or 4 consecutive work items per workgroup, loaded straight into the
 // first stage's registers.
 template <typename T, int LOGR>
 __global__ __launch_bounds__(fft_threads<T>(LOGR + log_cols(sizeof(T) == 8 ? CM_C64 : CM_C128, LOGR))) void k_fft_next(
@@ -835,8 +834,8 @@ static constexpr std::array<decltype(&k_fft_first<T, WIDE_B, true>), sizeof...(B
   return {&k_fft_first<T, WIDE_B0 + B, true>...};
 }
 template <typename T, int... B>
-static constexpr std::array<decltype(&k_fft_next<T, 1>), sizeof...(B)> next_table(std::integer_sequence<int, B...>) {
-  return {&k_fft_next<T, B + 1>...};
+static constexpr std::array<decltype(&k_fft_next<T, LATER_MIN_BITS>), sizeof...(B)> next_table(std::integer_sequence<int, B...>) {
+  return {&k_fft_next<T, LATER_MIN_BITS + B>...};
 }
 
 // Prices of the chosen strikes from the transform: price u = 2 v + c is component c of g_v.
@@ -889,18 +888,18 @@ static cm_status fft_run(const cm_problem *prob, int batch, int n, const int64_t
   constexpr int FB = first_radix_bits(dtype), NB = later_radix_bits(dtype);
   static constexpr auto kfirst = first_table<T>(std::make_integer_sequence<int, FB + 1>{});
   static constexpr auto kwide = wide_table<T>(std::make_integer_sequence<int, WIDE_B - WIDE_B0 + 1>{});
-  static constexpr auto knext = next_table<T>(std::make_integer_sequence<int, NB>{});
+  static constexpr auto knext = next_table<T>(std::make_integer_sequence<int, NB - LATER_MIN_BITS + 1>{});
   const int lr0 = p.logr[0];
   if (lr0 < 0 || lr0 > FB) return CM_E_UNSUPPORTED;
   for (int ps = 1; ps < p.npass; ++ps)
-    if (p.logr[ps] < 1 || p.logr[ps] > NB) return CM_E_UNSUPPORTED;
+    if (p.logr[ps] < LATER_MIN_BITS || p.logr[ps] > NB) return CM_E_UNSUPPORTED;
   const size_t lds0 = first_lds_bytes<T>(lr0);
   const bool wide = p.npass == 1 && lr0 >= WIDE_B0 && lr0 <= WIDE_B && batch <= WIDE_GRIDS;
   const auto first = wide ? kwide[lr0 - WIDE_B0] : kfirst[lr0];
   const int nt0 = wide ? wide_threads(lr0) : first_threads<T>(lr0);
   CM_HIP_CHECK(cm_allow_lds(first, lds0));
   for (int ps = 1; ps < p.npass; ++ps)
-    CM_HIP_CHECK(cm_allow_lds(knext[p.logr[ps] - 1], lds_bytes(p.logr[ps], 1 << log_cols(dtype, p.logr[ps]), sizeof(T))));
+    CM_HIP_CHECK(cm_allow_lds(knext[p.logr[ps] - LATER_MIN_BITS], lds_bytes(p.logr[ps], 1 << log_cols(dtype, p.logr[ps]), sizeof(T))));
   for (int inst0 = 0; inst0 < batch; inst0 += p.chunk) {
     const int cnt = (batch - inst0) < p.chunk ? (batch - inst0) : p.chunk;
     P *dstp = (P *)prices + (int64_t)inst0 * M;   // where the last pass writes prices
@@ -912,7 +911,7 @@ static cm_status fft_run(const cm_problem *prob, int batch, int n, const int64_t
     for (int ps = 1; ps < p.npass; ++ps) {
       const int lr = p.logr[ps], lc = log_cols(dtype, lr);
       const bool to_prices = ps == p.npass - 1 && !gather;
-      hipLaunchKernelGGL(knext[lr - 1], dim3((unsigned)((N >> lr) >> lc), cnt), dim3(fft_threads<T>(lr + lc)),
+      hipLaunchKernelGGL(knext[lr - LATER_MIN_BITS], dim3((unsigned)((N >> lr) >> lc), cnt), dim3(fft_threads<T>(lr + lc)),
                          lds_bytes(lr, 1 << lc, sizeof(T)), s, dp, inst0, n, plen, buf[cur], buf[cur ^ 1],
                          to_prices ? dstp : (P *)nullptr);
       CM_LAUNCH_CHECK();

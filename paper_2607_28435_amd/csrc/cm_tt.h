@@ -84,9 +84,6 @@ __host__ __device__ __forceinline__ double strike_log(double k0, const StrikeSte
   two_sum(k0, p, sm, t);
   return sm + (t + e);
 }
-__host__ __device__ __forceinline__ double strike_log(double k0, double eta, int n, double u) {
-  return strike_log(k0, strike_step(eta), n, u);
-}
 
 // ------------------------------------------------------------------ rounding sweep
 // Per-workgroup scratch for one rounding job (FP64 complex, global memory). `tt` holds n
