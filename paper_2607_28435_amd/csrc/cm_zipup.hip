@@ -1006,11 +1006,13 @@ __global__ __launch_bounds__(64, 2) void k_zip_left(TTView w, int w_slots, TTVie
   }
 }
 
-// LEFT: k_zip_left has run before (a switch at run time spills 56 registers instead of 51 for every batch).
+// LEFT: k_zip_left has run before. The batches without it have their own instantiation, since the mark
+// costs 5 more spilled registers (56 instead of 51). In the other one the switch stays the argument `left`: with
+// it folded away the compiler schedules the pivot loops otherwise, 4.75 against 4.66 ms (4096 trains, n = 24).
 template <typename T, bool LEFT>
 __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTView x, TTView y, double tol, int cap,
                                                  int batch, int32_t *__restrict__ status,
-                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap) {
+                                                 char *__restrict__ ws, size_t slab_bytes, int64_t mat_cap, int left) {
   extern __shared__ __align__(16) char lds_arena[];
   __shared__ la::Sh sh;
   __shared__ int code_sh;
@@ -1053,7 +1055,7 @@ __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTVie
     }
     const double delta2 = (n > 1) ? tol * tol * xn2_sh / (double)(n - 1) : 0.0;
     // where k_zip_left stopped: its carry moves from y's core l0 to the slab
-    const int mark = LEFT ? -y.rk(b)[n] : 0;
+    const int mark = LEFT && left ? -y.rk(b)[n] : 0;
     const int l0 = mark > 0 ? (mark - 1) & 63 : 0;
     int chi = l0 > 0 ? y.rk(b)[l0] : 1;
     if (l0 > 0) {
@@ -1066,7 +1068,7 @@ __global__ __launch_bounds__(CM_WG, 3) void k_zipup(TTView w, int w_slots, TTVie
       y.rk(b)[0] = 1;
     }
     __syncthreads();
-    if (LEFT && tid == 0) y.rk(b)[n] = 1;   // a rank again, also for a chain that ends early
+    if (LEFT && left && tid == 0) y.rk(b)[n] = 1;   // a rank again, also for a chain that ends early
     for (int l = l0; l < n; ++l) {
       SiteDims sd;
       sd.chi = chi; sd.w0 = wr[l]; sd.w1 = wr[l + 1]; sd.r0 = xr[l]; sd.r1 = xr[l + 1];
@@ -1148,7 +1150,7 @@ static cm_status zip_apply(const cm_tt_batch *w_by_n, const cm_tt_batch *x, doub
       hipLaunchKernelGGL(k_zip_left<T>, dim3(batch), dim3(64), zleft_lds<T>(), s, vw, w_by_n->batch, vx, vy, tol,
                          cap_rank, y->cap_rank);
     hipLaunchKernelGGL((k_zipup<T, LEFT>), dim3(slots), dim3(CM_WG), zlds_bytes<T>(), s, vw, w_by_n->batch, vx, vy, tol,
-                       cap_rank, batch, status, (char *)ws, slab, mc);
+                       cap_rank, batch, status, (char *)ws, slab, mc, (int)LEFT);
     return CM_OK;
   };
   const cm_status e = x->dtype == CM_C64 ? (left ? launch(float2{}, std::true_type{}) : launch(float2{}, std::false_type{}))
