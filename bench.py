@@ -557,9 +557,9 @@ def paper_curves(cm, torch, ns, dense_max, tol=1e-10, mpo_tol=None, reps=3, shot
 BF16_DENSE_TFLOPS = 2500.0
 
 # HBM bytes per dispatch from the rocprofv3 FETCH_SIZE / WRITE_SIZE runs recorded in
-# profiles/traffic_pmc_heston4096_n24.md (fetch scaled by 2.0 and write by 1.0, the factors a
-# 1 GiB device copy gives). A figure is reported only while the kernel's sources hash to the
-# value they had when the counters were taken.
+# profiles/traffic_pmc_heston4096_n24.md and profiles/traffic_pmc_surrogate_infer.md (fetch
+# scaled by 2.0 and write by 1.0, the factors a 1 GiB device copy gives). A figure is reported
+# only while the kernel's sources hash to the value they had when the counters were taken.
 ZIPUP_SOURCES = ["paper_2607_28435_amd/csrc/cm_zipup.hip", "paper_2607_28435_amd/csrc/cm_tt.h",
                  "paper_2607_28435_amd/csrc/cm_linalg.h", "paper_2607_28435_amd/csrc/cm_internal.h", "include/cm.h"]
 FFT_SOURCES = ["paper_2607_28435_amd/csrc/cm_fft.hip", "paper_2607_28435_amd/csrc/cm_cf.h",
@@ -580,19 +580,22 @@ MLP_SOURCES = ["paper_2607_28435_amd/csrc/cm_mlp.hip", "paper_2607_28435_amd/csr
 _F = 1.9999246625669753   # FETCH_SIZE scale of the 1 GiB copy (chain runs)
 _FS = 1.999924424166386  # the same for the surrogate runs
 PROFILED_TRAFFIC = {
-    "k_zipup": {"sha": "e7e1d79ec8558963", "bytes": (199956.9 * _F + 849972.8) * 1024,
-                "per": "launch (4096 instances, n=24, 1536 workgroups)"},
-    "build": {"sha": "9ae1b95f36b0a318", "bytes": ((37192.0 + 401323.2) * _F + 229858.3 + 816959.3) * 1024,
+    "k_zipup": {"sha": "a51c888e87c99862", "bytes": ((40575.4 + 272387.8) * _F + 107138.6 + 841448.3) * 1024,
+                "per": "launch (k_zip_left + k_zipup, 4096 instances, n=24, 1536 workgroups)"},
+    "build": {"sha": "573977d2e939d402", "bytes": ((37178.9 + 400855.4) * _F + 229917.0 + 817038.2) * 1024,
               "per": "build (k_build_qtt + k_build_round, 4096 instances, n=24)"},
-    "k_tt_round": {"sha": "b814f698d2149b43", "bytes": (241047.6 * _F + 417431.9) * 1024,
+    "k_tt_round": {"sha": "d64fc59291112e09", "bytes": (241163.4 * _F + 417414.6) * 1024,
                    "per": "launch (4096 instances, n=24, 4096 workgroups)"},
-    "k_readout": {"sha": "a8120f97e9153a98", "bytes": ((787.8 + 105182.8 + 788.6) * _F + 131072.0) * 1024,
+    "k_readout": {"sha": "f1ffd14cbed3a8f3", "bytes": ((788.8 + 105900.2 + 786.6) * _F + 131072.0) * 1024,
                   "per": "read-out (k_readout<8> + <16> + <32>, 4096 instances x 4096 strikes)"},
-    "dense": {"sha": "9662f05dd5eaea99", "bytes": ((157.5 + 65631.0) * _F + 131080.25 + 65536.0) * 1024,
-              "per": "grid (k_fft_first + k_fft_next, n=24)"},
-    "k_sample": {"sha": "b563430d544ae401", "bytes": (3780258.8 * _F + 131072.0) * 1024,
-                 "per": "launch (4096 instances x 4096 shots, n=24)"},
-    "surrogate": {"sha": "60db21156adabfa7", "bytes": ((16041.5 + 16407.0) * _FS + 4096.0 + 8192.0) * 1024,
+    "dense": {"sha": "758160f7f053fee9", "bytes": ((342.0 + 32919.5) * _F + 65536.0 + 65536.0) * 1024,
+              "per": "grid (k_fft_first + k_fft_next, n=24, all strikes)"},
+    "k_sample": {"sha": "bff6a6f00be30b1d",
+                 "bytes": ((3286203.3 + 2458.6 + 2452.3 + 2194.6 + 2197.1) * _F + 887889.2) * 1024,
+                 "per": "launch (k_sample<4> .. <32>, 4096 instances x 4096 shots, n=24)"},
+    # k_mlp_fused: the mean of 101 passes over 2^20 queries and one over 2^15, by rows
+    "surrogate": {"sha": "15b54175796a8079",
+                  "bytes": ((15880.4 * 102 / (101 + 1 / 32) + 16407.0) * _FS + 4096.0 + 8192.0) * 1024,
                   "per": "pass over 2^20 queries (k_mlp_fused + k_gate)"},
 }
 
@@ -858,7 +861,7 @@ def main():
         "build": alu_roofline("k_build_qtt + k_build_round (cm_build_qtt)", ms["build"], 0.0, SURVEY_BUILD_F64 * B,
                               es * b_x + 128 * B, "build", BUILD_SOURCES,
                               extra={"flops_model": "scope-table estimate, 3e6 FP64 per grid"}),
-        "zipup": alu_roofline("k_zipup (cm_sfft_apply)", ms["apply"], f32, f64, es * (b_x + b_yz), "k_zipup",
+        "zipup": alu_roofline("k_zip_left + k_zipup (cm_sfft_apply)", ms["apply"], f32, f64, es * (b_x + b_yz), "k_zipup",
                               ZIPUP_SOURCES, extra={
                                   "flops_model": "rank-exact (zipup_flops)",
                                   "frac_scope_formula": ((SURVEY_ZIPUP_F32 / (FP32_VECTOR_TFLOPS * 1e12) +
@@ -921,7 +924,7 @@ def main():
         "status_errors": bad,
         "ranks": {"x_max": int(xr[:, :args.n + 1].max()), "y_max": int(yr[:, :args.n + 1].max()),
                   "w_max": int(wr[:args.n + 1].max())},
-        "roofline": {"kernel": "k_zipup (cm_sfft_apply)", "bound": "alu", "achieved": achieved_tf,
+        "roofline": {"kernel": "k_zip_left + k_zipup (cm_sfft_apply)", "bound": "alu", "achieved": achieved_tf,
                      "peak": FP64_VECTOR_TFLOPS, "unit": "TFLOP/s", "frac": frac,
                      "traffic": profiled_traffic("k_zipup", ZIPUP_SOURCES),
                      "traffic_per": PROFILED_TRAFFIC["k_zipup"]["per"],

@@ -348,9 +348,10 @@ __global__ __launch_bounds__(512, 1) void k_mlp_fused(const float *__restrict__ 
 // layer are loaded while the present one finishes, and the values alternate between two LDS
 // buffers, so a layer costs one barrier. 8192 rows are 256 tiles, one per CU; a launch per layer
 // with the weights staged in LDS put one 32-row tile on two of sixteen waves behind 128 KB of
-// staging. 8192 rows: forward with the pre-activations stored 18.5 us (58 before), backward
-// chain 31 us (107 before, its first-layer gradients included); 777 rows of inference 9.6 us
-// (27 with tiles of 64). Bound by the latency of a layer (fragments, products, epilogue).
+// staging. 8192 rows: forward with the pre-activations stored 21 us (58 before), backward
+// chain 33 us (107 before, its first-layer gradients included); 777 rows of inference 9.6 us
+// (27 with tiles of 64). Bound by the latency of a layer (fragments, products, epilogue): at 8192
+// rows two waves a SIMD, 17 % of its cycles issuing VALU instructions.
 constexpr int TM = 32;
 constexpr int TWG = 512;
 constexpr int TKS = NW / 16;                                        // K steps per layer
@@ -698,10 +699,11 @@ __global__ __launch_bounds__(TWG) void k_mlp_bwd(const float *__restrict__ x, co
 // in registers. Each wave converts one of the four 32-column blocks of either operand and
 // shares the fragments through LDS, so nothing is loaded or converted twice in a workgroup; the
 // next rows' loads are in flight during the products. delta_4 is formed here from dy and Z4.
-// 8192 rows take 35 us for all layers, about 10 of them the 6.3 M atomics of 32 spans (16 spans
-// 53 us: too few workgroups; 64 about 10 us more atomics); it is bound by the latency of a step's
-// loads. It replaces, per layer, a 64 x 64-tile kernel that converted each element in four
-// workgroups (44 us) and a column sum (19 us).
+// 8192 rows take 39 us for all layers (35 with the fast SiLU also in W5's gradient and the deltas),
+// about 10 of them the 6.3 M atomics of 32 spans (16 spans 53 us against those 35: too few workgroups;
+// 64 about 10 us more atomics); it is bound by the latency of a step's loads. It replaces, per layer,
+// a 64 x 64-tile kernel that converted each element in four workgroups (44 us) and a column sum
+// (19 us).
 constexpr int GWT = 128;                  // tile edge
 constexpr int GKR = 32;                   // rows per step
 constexpr int WG_SPANS = 32;              // spans of rows (see cm_mlp_backward)

@@ -652,8 +652,11 @@ __device__ __forceinline__ int zip_site_pair(char *arena, const SiteDims &sd, co
 // waves most lanes hold no column and a pivot step is a chain of barrier, candidate exchange and
 // reductions. Here one 64-lane workgroup takes an instance through these sites: eight lanes per
 // column as in zip_site_pair<4, 8> (row 8 s + g in slot s of lane g), but columns q, q + 8, ... on
-// the group q, so every column's arithmetic, and with it every core, is that kernel's bit for
-// bit, the pivot search stays in the wave, and eight instances share a CU instead of three
+// the group q, so every column goes through that kernel's operations in their order and the pivots
+// are chosen by the same rule. Last bits may differ, and with them a rank at the very edge of the
+// tolerance: the tail's norms are summed over the columns in another order, and the compiler fuses
+// other products into multiply-adds. The pivot search stays in the wave, and eight instances share a
+// CU instead of three
 // (235 VGPRs; bounded to 168 it spills and measured 5.74 against 5.51 ms, with columns up to 16 at
 // 128 VGPRs 5.79). A site costs about 50 K cycles: staging 4, contraction 11, 8.9 pivot steps of
 // 3.2, Q 10; it is bound by the latency of these chains.
